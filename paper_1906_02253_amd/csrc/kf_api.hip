@@ -138,7 +138,6 @@ int prepare_find(kf_ctx* ctx, const kf_hits* hits, const int32_t* event_off, int
         return fail(ctx, KF_EINVAL, "%s: null seed_event, seed_hits or out_hits", what);
     const int W = ctx->find_width;
     const int MC = ctx->params.max_cands;
-    const int S = kfmi::seeds_per_wg(W, MC);
     const int nl = ctx->n_layers;
     kfmi::FindPlan& pl = L->pl;
     int64_t per_event = 0;
@@ -150,7 +149,7 @@ int prepare_find(kf_ctx* ctx, const kf_hits* hits, const int32_t* event_off, int
         (int64_t)n_events * 4096 >= 0x7fffffffLL)
         return fail(ctx, KF_EINVAL, "%s: n_events x bins per event exceeds 2^31", what);
     pl.bl.per_event = (int32_t)per_event;
-    const size_t lds = kfmi::find_shared_size(W, S, nl, prec);
+    const size_t lds = kfmi::find_shared_size(W, nl, prec);
     if (ctx->max_lds > 0 && lds > (size_t)ctx->max_lds)
         return fail(ctx, KF_EUNSUPPORTED, "%s: width %d needs %zu bytes of LDS, device allows %d",
                     what, W, lds, ctx->max_lds);
@@ -161,15 +160,29 @@ int prepare_find(kf_ctx* ctx, const kf_hits* hits, const int32_t* event_off, int
     const bool steer = ctx->d_steer != nullptr;
     int& occ = ctx->occ_cache[field ? 1 : 0][steer ? 1 : 0][mat ? 1 : 0][learn ? 1 : 0][pi][lw];
     if (occ == 0) {
-        hipError_t e = kfmi::find_max_blocks_per_cu(W, S, nl, prec, learn, mat, steer, field, &occ);
+        hipError_t e = kfmi::find_max_blocks_per_cu(W, nl, prec, learn, mat, steer, field, &occ);
         if (e != hipSuccess) return hip_fail(ctx, e, "find occupancy");
         if (occ < 1) occ = 1;
     }
-    const int64_t n_tiles = (seeds->n + S - 1) / S;
-    int64_t grid = (int64_t)occ * (ctx->n_cu > 0 ? ctx->n_cu : 1);
-    if (grid > n_tiles) grid = n_tiles;
-    if (grid < 1) grid = 1;
-    const size_t bytes = kfmi::plan_find(&pl, nullptr, hits->n, n_events, seeds->n, nl, (int)grid, S);
+    // A tile of the finding kernel is one wave's seeds, SPW at most.  With fewer
+    // seeds than the resident waves hold, the tiles get smaller: a wave's lanes
+    // scan the hits of all its candidates' windows together, so that a step of
+    // one seed alone is the shortest.
+    const int nw = (W + 63) / 64, SPW = kfmi::seeds_per_wave(W, MC);
+    const int64_t resident = (int64_t)occ * (ctx->n_cu > 0 ? ctx->n_cu : 1);
+    int64_t TS = (seeds->n + resident * nw - 1) / (resident * nw);
+    TS = TS < 1 ? 1 : (TS > SPW ? SPW : TS);
+    int64_t n_tiles = 0, grid = 0;
+    size_t bytes = 0;
+    for (;;) {
+        n_tiles = (seeds->n + TS - 1) / TS;
+        grid = (n_tiles + nw - 1) / nw < resident ? (n_tiles + nw - 1) / nw : resident;
+        if (grid < 1) grid = 1;
+        bytes = kfmi::plan_find(&pl, nullptr, hits->n, n_events, seeds->n, nl, (int)grid * nw, (int)TS);
+        // a fixed scratch too small for this many tiles may hold the full ones
+        if (!fixed_ws || bytes <= fixed_bytes || TS == SPW) break;
+        TS = SPW;
+    }
     void* base = nullptr;
     if (fixed_ws) {
         if (bytes > fixed_bytes)
@@ -180,7 +193,7 @@ int prepare_find(kf_ctx* ctx, const kf_hits* hits, const int32_t* event_off, int
         base = ctx->ws.get(bytes);
         if (!base) return fail(ctx, KF_ENOMEM, "%s: workspace of %zu bytes", what, bytes);
     }
-    kfmi::plan_find(&pl, base, hits->n, n_events, seeds->n, nl, (int)grid, S);
+    kfmi::plan_find(&pl, base, hits->n, n_events, seeds->n, nl, (int)grid * nw, (int)TS);
     kfmi::FindArgs& a = L->a;
     a.bh = (const kfmi::BinnedHit*)pl.binned;
     a.bin_off = pl.off;
@@ -216,7 +229,7 @@ int prepare_find(kf_ctx* ctx, const kf_hits* hits, const int32_t* event_off, int
     a.mat = ctx->mat;
     a.steer = ctx->d_steer;
     a.n_tiles = (int)n_tiles;
-    a.seeds_per_tile = S;
+    a.seeds_per_tile = (int)TS;
     a.mlp = ctx->mlp.dev();
     L->learn = learn;
     L->clean = (flags & KF_CLEAN_SEEDS) != 0;
@@ -250,7 +263,7 @@ hipError_t phase_order(const kf_ctx* ctx, const kfmi::FindLaunch& L, hipStream_t
         e = kfmi::launch_clean(L.pl, L.seeds, L.seed_event, (int)L.n_events, L.seed_hits,
                                L.hits->n, ctx->params, s);
     if (e == hipSuccess) e = kfmi::launch_cost_order(L.pl, L.seeds, L.a.n_tiles, L.a.seeds_per_tile, s);
-    if (e == hipSuccess) e = kfmi::launch_fill(L.pl.tile_counter, 64, 0, s);
+    if (e == hipSuccess) e = kfmi::launch_fill(L.pl.tile_counter, kfmi::kQueues * kfmi::kQueueStride, 0, s);
     return e;
 }
 
@@ -464,7 +477,7 @@ int kf_set_find_config(kf_ctx* ctx, int32_t width, int32_t largest_first)
     if (!ctx) return fail(nullptr, KF_EINVAL, "kf_set_find_config: null context");
     if (width != 32 && width != 64 && width != 128 && width != 256)
         return fail(ctx, KF_EINVAL, "kf_set_find_config: width must be 32, 64, 128 or 256");
-    if (kfmi::seeds_per_wg(width, ctx->params.max_cands) < 1)
+    if (kfmi::seeds_per_wave(width, ctx->params.max_cands) < 1)
         return fail(ctx, KF_EINVAL, "kf_set_find_config: width below max_cands");
     ctx->find_width = width;
     ctx->find_largest_first = largest_first ? 1 : 0;
@@ -869,9 +882,9 @@ int kf_autotune(kf_ctx* ctx, const kf_hits* hits, const int32_t* event_off, int3
     for (int c = 0; c < NC; ++c) {
         best_ms[c] = -1.0f;
         const int w = widths[c / 2];
-        fits[c] = kfmi::seeds_per_wg(w, ctx->params.max_cands) >= 1 &&
+        fits[c] = kfmi::seeds_per_wave(w, ctx->params.max_cands) >= 1 &&
                   !((flags & KF_INIT_MLP) && w < 64) &&
-                  kfmi::find_shared_size(w, kfmi::seeds_per_wg(w, ctx->params.max_cands), ctx->n_layers,
+                  kfmi::find_shared_size(w, ctx->n_layers,
                                          flags & KF_PREC_MASK) <= (size_t)ctx->max_lds;
     }
     // configurations are visited round-robin, reps rounds, each call timed

@@ -24,7 +24,6 @@
 namespace kfmi {
 
 static_assert(sizeof(BinnedHit) == 32, "BinnedHit is two 16-byte loads");
-constexpr int kQueues = 8;     // tile queues, one per XCD
 
 // ------------------------------------------------------------------ binning
 __device__ inline int phi_bin_of(float phi, int nb)
@@ -582,6 +581,13 @@ __device__ inline uint64_t merge_key(int nhits, float c2, int j, int c)
            ((uint64_t)c << 8);
 }
 
+// The chi2 in a selection key (its float bits made monotone).
+__device__ inline float merge_key_chi2(uint64_t key)
+{
+    const uint32_t u = (uint32_t)(key >> 24);
+    return __uint_as_float((u & 0x80000000u) ? (u & 0x7FFFFFFFu) : ~u);
+}
+
 // Row stride of the window owners' position covariance in LDS: six values
 // padded to whole 16-byte reads (three for FP64, two for FP32)
 template <typename C> constexpr int kOwnCov = sizeof(C) == 8 ? 6 : 8;
@@ -599,59 +605,49 @@ __device__ inline void load_owner_cov(const C* r, C pc[6])
     }
 }
 
-// LDS layout of one workgroup (W lanes); arrays lane-minor unless noted
-template <typename C>
-struct FindShared {
-    C* ocov;            // [W][kOwnCov] window owner's predicted position covariance
-                        //          P00 P01 P02 P11 P12 P22 (16-byte rows)
-    float* pchi2;       // [W]      chi2 of each lane's candidate
-    int32_t* meta;      // [4][W]   nhits, misses, status, (done | (layer + 1) << 8)
-    float* cchi2;       // [kMaxCands][W]  accepted hit chi2, ascending
-    int32_t* cbidx;     // [kMaxCands][W]  binned index of those hits
-    int32_t* nchild;    // [W]
-    int8_t* sel;        // [S][kMaxCands][2]  (parent slot, child index)
-    int32_t* nsel;      // [S]
-    kf_layer* layers;   // [n_layers]
-    NavOrder* nav;      // surface orders of the dynamic navigation
-    int32_t* misc;      // [4] the tile: first position in the order, seed count
-    // cooperative window scan, per lane (owner of a window) and per wave
-    float* orec;        // [W][8] window owner record: predicted x, y, z, cos and sin of its
-                        //        azimuth, sin(dphi), wv, flags (two 16-byte reads)
-    int32_t* seg;       // [n_waves][3][kSeg] queued phi rows: owner lane, first hit, count
-    int32_t* segpre;    // [n_waves][kSeg + 1] prefix of the rows' hit counts
-    int32_t* acc;       // [n_waves][3][kAcc] per owner lane its accepted hits' first and last
-                        // entry ([0, 64), [64, 128)); the entries' hit index; their binned index
-    float* accc2;       // [n_waves][kAcc] their chi2
-    int32_t* rowp;      // [n_waves][5][64] per owner lane: row prefix, first row, bins, base, sizes
-};
-
 constexpr int kSeg = 128;       // phi rows queued per wave per round
 constexpr int kScanBatch = 4;   // hits per lane in flight in the scan
 constexpr int kAcc = 64 * kScanBatch;
 constexpr int kInsBatch = 4;    // accepted hits an owner loads together
+constexpr int kSelKeys = 64 * (kMaxCands + 1);   // children of a wave's candidates, at most
 
-__host__ __device__ inline size_t find_shared_bytes(int W, int S, int nl, size_t csize)
+// LDS of one wave; arrays lane-minor unless noted.  The window scan's queues
+// and the selection's keys are never live together.
+template <typename C>
+struct alignas(16) WaveLds {
+    C ocov[64 * kOwnCov<C>];    // window owner's predicted position covariance
+                                //          P00 P01 P02 P11 P12 P22 (16-byte rows)
+    float orec[64 * 8];         // window owner record: predicted x, y, z, cos and sin of its
+                                //        azimuth, sin(dphi), wv, flags (two 16-byte reads)
+    union {
+        struct {
+            int32_t seg[3 * kSeg];      // queued phi rows: owner lane, first hit, count
+            int32_t segpre[kSeg + 4];   // prefix of the rows' hit counts
+            int32_t acc[3 * kAcc];      // per owner lane its accepted hits' first and last entry
+                                        // ([0, 64), [64, 128)); the entries' hit index; their
+                                        // binned index
+            float accc2[kAcc];          // their chi2
+            int32_t rowp[5 * 64];       // per owner lane: row prefix, first row, bins, base, sizes
+        };
+        struct {
+            uint64_t key[kSelKeys];     // [seeds][max_cands (max_cands + 1)] a seed's children
+            uint64_t sel[64];           // [seeds][max_cands] its survivors, best first
+            int32_t cbidx[kMaxCands * 64];   // binned index of each candidate's accepted hits
+        };
+    };
+};
+
+// LDS of a workgroup: the layers, the navigation's surface orders, then each
+// wave's own block
+__host__ __device__ inline size_t find_layers_bytes(int nl)
 {
-    size_t b = 0;
-    b += csize * (csize == 8 ? 6 : 8) * W;
-    b += sizeof(float) * W;
-    b += sizeof(int32_t) * 4 * W;
-    b += sizeof(float) * kMaxCands * W;
-    b += sizeof(int32_t) * kMaxCands * W;
-    b += sizeof(int32_t) * W;
-    b += sizeof(int32_t) * S;
-    b = (b + 15) & ~size_t(15);
-    b += sizeof(kf_layer) * nl;
-    b += sizeof(NavOrder);
-    b += sizeof(int32_t) * 4;
-    b += 2 * S * kMaxCands;
-    b = (b + 15) & ~size_t(15);
-    const size_t nw = (W + 63) / 64;
-    b += sizeof(float) * 8 * W;
-    b += sizeof(int32_t) * nw * (3 * kSeg + kSeg + 1 + 3 * kAcc);
-    b += sizeof(float) * nw * kAcc;
-    b += sizeof(int32_t) * nw * 5 * 64;
-    return (b + 15) & ~size_t(15);
+    return (sizeof(FindLayer) * nl + nav_bytes(nl) + 15) & ~size_t(15);
+}
+
+template <typename C>
+__host__ __device__ inline size_t find_shared_bytes(int W, int nl)
+{
+    return find_layers_bytes(nl) + sizeof(WaveLds<C>) * ((W + 63) / 64);
 }
 
 // waves per SIMD the register allocation is held to (a build-time tuning knob)
@@ -667,80 +663,70 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
     const int W = blockDim.x;
     const int S = a.seeds_per_tile;
     const int MC = a.prm.max_cands;
+    const int SPW = seeds_per_wave(W, MC);
     const int nl = a.n_layers;
     // seeds and outputs are stored in T; in registers a candidate's state is
     // held in T and its covariance in C (the update runs in U)
     const T* scov = (const T*)a.scov;
     T* ocov = (T*)a.ocov;
-    FindShared<C> sh;
-    {
-        unsigned char* q = smem;
-        sh.ocov = (C*)q;
-        q += sizeof(C) * kOwnCov<C> * W;
-        sh.pchi2 = (float*)q;
-        q += sizeof(float) * W;
-        sh.meta = (int32_t*)q;
-        q += sizeof(int32_t) * 4 * W;
-        sh.cchi2 = (float*)q;
-        q += sizeof(float) * kMaxCands * W;
-        sh.cbidx = (int32_t*)q;
-        q += sizeof(int32_t) * kMaxCands * W;
-        sh.nchild = (int32_t*)q;
-        q += sizeof(int32_t) * W;
-        sh.nsel = (int32_t*)q;
-        q += sizeof(int32_t) * S;
-        q = smem + (((size_t)(q - smem) + 15) & ~size_t(15));
-        sh.layers = (kf_layer*)q;
-        q += sizeof(kf_layer) * nl;
-        sh.nav = (NavOrder*)q;
-        q += sizeof(NavOrder);
-        sh.misc = (int32_t*)q;
-        q += sizeof(int32_t) * 4;
-        sh.sel = (int8_t*)q;
-        q += 2 * S * kMaxCands;
-        q = smem + (((size_t)(q - smem) + 15) & ~size_t(15));
-        const int nw = (W + 63) / 64;
-        sh.orec = (float*)q;
-        q += sizeof(float) * 8 * W;
-        sh.seg = (int32_t*)q;
-        q += sizeof(int32_t) * nw * 3 * kSeg;
-        sh.segpre = (int32_t*)q;
-        q += sizeof(int32_t) * nw * (kSeg + 1);
-        sh.acc = (int32_t*)q;
-        q += sizeof(int32_t) * nw * 3 * kAcc;
-        sh.accc2 = (float*)q;
-        q += sizeof(float) * nw * kAcc;
-        sh.rowp = (int32_t*)q;
-    }
+    const int nw = (W + 63) / 64;
     const int t = threadIdx.x;
-    for (int l = t; l < nl; l += W) sh.layers[l] = a.layers[l];
-    if (t == 0) build_nav_order(a.layers, nl, sh.nav);   // read after the tile loop's barrier
-    // seeds never straddle waves: wave w holds seeds w*SPW .. w*SPW + SPW - 1
-    const int SPW = seeds_per_wave(W, MC);
+    FindLayer* layers = (FindLayer*)smem;
+    void* nav_mem = smem + sizeof(FindLayer) * nl;
+    WaveLds<C>& w = ((WaveLds<C>*)(smem + find_layers_bytes(nl)))[t >> 6];
+    int nbarrel = 0;
+    for (int l = 0; l < nl; ++l) nbarrel += a.layers[l].kind == 0 ? 1 : 0;
+    for (int l = t; l < ((nl + 3) & ~3); l += W) {
+        nav_place(a.layers, nl, l, nav_mem);
+        if (l < nl) {
+            const kf_layer L = a.layers[l];
+            FindLayer f{};
+            f.r_or_z = float(L.r_or_z);
+            f.lo = float(L.lo);
+            f.hi = float(L.hi);
+            f.x0 = float(L.x0);
+            f.win_su = float(L.win_su);
+            f.win_sv = float(L.win_sv);
+            f.kind = L.kind;
+            f.nbin_phi = L.nbin_phi;
+            f.nbin_2 = L.nbin_2;
+            f.base = a.bl.base[l];
+            layers[l] = f;
+        }
+    }
+    const NavOrder nav = nav_view(nav_mem, nl, nbarrel);
+    __syncthreads();
+    // From here on the workgroup's waves never meet: a wave takes its own tiles
+    // and its lanes exchange through LDS and shuffles under wave-level fences,
+    // so that no wave waits for another's step and no step waits, as a
+    // workgroup barrier does, for its stores (the back-pointers) to be
+    // acknowledged.
     const int ln64 = t & 63;
-    const int s_loc = (t >> 6) * SPW + ln64 / MC;
+    const int s_loc = ln64 / MC;            // seed within the wave's tile
     const int slot = ln64 % MC;
-    const bool lane_ok = ln64 / MC < SPW && s_loc < S;
-    const int lbase = t - slot;             // lane of this seed's slot 0
+    const bool lane_ok = s_loc < SPW;
+    const int lbase = ln64 - slot;          // lane of this seed's slot 0
     const T kb = T(kKappa) * T(a.prm.bz);
     const float cut = float(a.prm.chi2_cut);
     unsigned n_prop = 0, n_upd = 0, n_chi2 = 0, n_kept = 0;   // per lane: far below 2^32
     int n_newton = 0, n_disk = 0, n_guess = 0, n_fallback = 0;
-    int2* bp_base = a.bp + (size_t)blockIdx.x * nl * S * kMaxCands;
+    int2* bp_base = a.bp + ((size_t)blockIdx.x * nw + (t >> 6)) * nl * S * kMaxCands;
 
+    // The processing order is split into kQueues contiguous ranges of whole
+    // tiles, one per XCD (workgroups are dispatched to the XCDs round-robin), so
+    // that a range's neighbouring eta-phi tiles share that XCD's L2.  A range's
+    // costliest-class seeds, at its head, come in tiles of SL seeds, the rest in
+    // tiles of S.  The waves of a range's workgroups take its first tiles by
+    // their place, the others from the range's counter (one cache line each),
+    // and a wave whose range is exhausted takes tiles from the others; no
+    // counter is touched for a range whose tiles are all taken by place.
+    const int64_t cs = (int64_t)((a.n_tiles + kQueues - 1) / kQueues) * S;
+    const int SL = looper_tile_seeds(S);
+    const int home = blockIdx.x % kQueues;
+    bool first = true;
     for (;;) {
-        __syncthreads();
-        if (t == 0) {
-            // the processing order is split into kQueues contiguous ranges of
-            // whole tiles, one per XCD (workgroups are dispatched to the XCDs
-            // round-robin), so that a range's neighbouring eta-phi tiles share
-            // that XCD's L2; a workgroup whose range is exhausted takes tiles
-            // from the others.  A range's costliest-class seeds, at its head,
-            // come in tiles of SL seeds, the rest in tiles of S.
-            const int64_t cs = (int64_t)((a.n_tiles + kQueues - 1) / kQueues) * S;
-            const int SL = looper_tile_seeds(S);
-            const int home = blockIdx.x % kQueues;
-            int start = -1, cnt = 0;
+        int tstart = -1, tcount = 0;
+        if (ln64 == 0) {
             for (int d = 0; d < kQueues; ++d) {
                 const int q = (home + d) % kQueues;
                 const int64_t lo = q * cs;
@@ -750,24 +736,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
                 int c0 = a.queue_loopers[q];
                 c0 = c0 < 0 ? 0 : (c0 > nq ? nq : c0);
                 const int nlt = (c0 + SL - 1) / SL;
-                const int i = atomicAdd(&a.tile_counter[q], 1);
+                const int ntq = nlt + (nq - c0 + S - 1) / S;
+                // waves at home in this range, and the tile of this one's place
+                const int placed = ((int)gridDim.x - q + kQueues - 1) / kQueues * nw;
+                int i = ((int)blockIdx.x / kQueues) * nw + (t >> 6);
+                if (!(first && d == 0)) {
+                    if (placed >= ntq) continue;
+                    i = placed + atomicAdd(&a.tile_counter[q * kQueueStride], 1);
+                }
                 if (i < nlt) {
-                    start = (int)lo + i * SL;
-                    cnt = c0 - i * SL < SL ? c0 - i * SL : SL;
+                    tstart = (int)lo + i * SL;
+                    tcount = c0 - i * SL < SL ? c0 - i * SL : SL;
                     break;
                 }
                 const int64_t j0 = c0 + (int64_t)(i - nlt) * S;   // first seed of a full tile
                 if (j0 < nq) {
-                    start = (int)(lo + j0);
-                    cnt = nq - j0 < S ? (int)(nq - j0) : S;
+                    tstart = (int)(lo + j0);
+                    tcount = nq - j0 < S ? (int)(nq - j0) : S;
                     break;
                 }
             }
-            sh.misc[0] = start;
-            sh.misc[1] = cnt;
         }
-        __syncthreads();
-        const int tstart = sh.misc[0], tcount = sh.misc[1];
+        first = false;
+        tstart = __builtin_amdgcn_readfirstlane(tstart);
+        tcount = __builtin_amdgcn_readfirstlane(tcount);
         if (tstart < 0) break;
 
         const bool valid = lane_ok && s_loc < tcount;
@@ -788,6 +780,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
             for (int k = 0; k < 6; ++k) p[k] = T(a.spar[k * a.sld + sid]);
 #pragma unroll
             for (int k = 0; k < 21; ++k) P[k] = C(scov[k * a.sld + sid]);
+            poison_nonfinite(P);
             chi2 = a.schi2[sid];
             nhits = (a.sndf[sid] + 5) / 2;
             status = a.sstatus[sid] | (bad_event ? (uint32_t)KF_ST_BADINPUT : 0u);
@@ -834,15 +827,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
         int nsteps = 0;
         for (int step = 0; step < nl; ++step) {
             const bool live = occupied && !done;
-            if (!__syncthreads_or(live)) break;
+            if (__ballot(live) == 0) break;
             // ---- a3: navigate and propagate (LEARN: the whole wave first
             // evaluates the learned start of its candidates' barrel solves)
             T s_guess = T(-1);
             if (LEARN) {
                 float f[kMlpIn] = {0, 0, 0, 0, 0, 0, 0, 0};
-                const int bl = live ? next_barrel(p, sh.layers, *sh.nav) : -1;
-                if (bl >= 0) mlp_features(p, sh.layers[bl], a.prm, f);
-                const float y = mlp_wave(a.mlp, f);
+                const int bl = live ? next_barrel(p, nav) : -1;
+                if (bl >= 0) mlp_features(p, layers[bl], a.prm, f);
+                const float y = mlp_wave(a.mlp, f, __ballot(bl >= 0));
                 if (bl >= 0) {
                     s_guess = T(mlp_guess(f, y));
                     ++n_guess;
@@ -852,35 +845,39 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
             if (live) {
                 T s;
                 int layer;
+                T sth = T(0), cth = T(0);     // theta stays along the helix
+                if constexpr (!FIELD) Tr<T>::sincos_(p[5], &sth, &cth);
                 T fl = T(0);
                 T fq[6];
                 if constexpr (FIELD && STEER)
-                    layer = steer_next_field(p, sh.layers, a.steer->layers[rg], a.steer->len[rg], &pos,
+                    layer = steer_next_field(p, layers, a.steer->layers[rg], a.steer->len[rg], &pos,
                                              a.prm, &fl, fq, &status, &n_newton, &n_disk);
                 else if constexpr (FIELD)
-                    layer = navigate_field(p, sh.layers, nl, a.prm, &fl, fq, &status, &n_newton,
+                    layer = navigate_field(p, layers, nl, a.prm, &fl, fq, &status, &n_newton,
                                            &n_disk, s_guess >= T(0) ? s_guess / Tr<T>::sin_(p[5]) : T(-1),
                                            LEARN ? a.prm.mlp_max_iter : 0, &n_fallback);
                 else if constexpr (STEER)
-                    layer = steer_next(p, sh.layers, a.steer->layers[rg], a.steer->len[rg], &pos,
-                                       a.prm, kb, &s, &status, &n_newton, &n_disk);
+                    layer = steer_next(p, layers, a.steer->layers[rg], a.steer->len[rg], &pos,
+                                       a.prm, kb, sth, cth, &s, &status, &n_newton, &n_disk);
                 else
-                    layer = navigate(p, sh.layers, *sh.nav, a.prm, kb, &s, &status, &n_newton, &n_disk,
-                                     s_guess, LEARN ? a.prm.mlp_max_iter : 0, &n_fallback);
+                    layer = navigate(p, layers, nav, a.prm, kb, sth, cth, &s, &status, &n_newton,
+                                     &n_disk, s_guess, LEARN ? a.prm.mlp_max_iter : 0, &n_fallback);
                 if (layer < 0) {
                     done = true;
                 } else {
                     ++n_prop;
-                    const kf_layer L = sh.layers[layer];
+                    const FindLayer L = layers[layer];
                     if constexpr (FIELD)
                         field_transport(p, P, fq, fl, a.prm, L.kind, T(L.r_or_z));
                     else
-                        transport(p, P, s, kb, L.kind, T(L.r_or_z));
+                        transport(p, P, s, kb, L.kind, T(L.r_or_z), sth, cth);
                     if (a.material) {
                         if constexpr (MAT)
                             add_material(p, P, L, a.mat, T(a.prm.mass));
-                        else
+                        else if constexpr (FIELD)
                             add_scatter(p, P, L.kind, T(L.x0), T(a.prm.mass));
+                        else
+                            add_scatter(p, P, L.kind, T(L.x0), T(a.prm.mass), sth, cth);
                     }
                     bool fin = true;
 #pragma unroll
@@ -901,9 +898,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
             // lane inserts its own into its sorted list.
             if (lane_ok) {
 #pragma unroll
-                for (int k = 0; k < 3; ++k) sh.orec[t * 8 + k] = float(p[k]);
-                sh.pchi2[t] = chi2;
-                C* oc = sh.ocov + t * kOwnCov<C>;
+                for (int k = 0; k < 3; ++k) w.orec[ln64 * 8 + k] = float(p[k]);
+                C* oc = w.ocov + ln64 * kOwnCov<C>;
                 oc[0] = P[pk(0, 0)];
                 oc[1] = P[pk(0, 1)];
                 oc[2] = P[pk(0, 2)];
@@ -922,7 +918,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
             int nacc = 0;
             int nrow = 0, row_lo = 0, v0 = 0, v1 = 0, np = 1, n2 = 1, row0 = 0;
             if (pl >= 0) {
-                const kf_layer L = sh.layers[pl];
+                const FindLayer L = layers[pl];
                 const Window<T> Wn = make_window<T, C>(p, P, L, T(cut));
                 if (Wn.ok) {
                     np = L.nbin_phi;
@@ -941,30 +937,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
                     row_lo = b_lo;
                     v0 = coord_bin_of(float(Wn.vlo), float(L.lo), float(L.hi), n2);
                     v1 = coord_bin_of(float(Wn.vhi), float(L.lo), float(L.hi), n2);
-                    row0 = ev * a.bl.per_event + a.bl.base[pl];
+                    row0 = ev * a.bl.per_event + L.base;
                     const T rho = Tr<T>::sqrt_(p[0] * p[0] + p[1] * p[1]);
-                    sh.orec[t * 8 + 3] = float(p[0] / rho);
-                    sh.orec[t * 8 + 4] = float(p[1] / rho);
-                    sh.orec[t * 8 + 5] = float(Wn.sin_dphi);
-                    sh.orec[t * 8 + 6] = float(Wn.wv);
-                    sh.orec[t * 8 + 7] = __int_as_float((Wn.all_phi ? 1 : 0) | (L.kind << 1));
+                    w.orec[ln64 * 8 + 3] = float(p[0] / rho);
+                    w.orec[ln64 * 8 + 4] = float(p[1] / rho);
+                    w.orec[ln64 * 8 + 5] = float(Wn.sin_dphi);
+                    w.orec[ln64 * 8 + 6] = float(Wn.wv);
+                    w.orec[ln64 * 8 + 7] = __int_as_float((Wn.all_phi ? 1 : 0) | (L.kind << 1));
                 }
             }
             {
-                const int wave = t >> 6, ln = t & 63;
-                const int wlanes = (W - (wave << 6)) < 64 ? (W - (wave << 6)) : 64;
-                int32_t* sg_own = sh.seg + wave * 3 * kSeg;
+                const int ln = ln64;
+                const int wlanes = W < 64 ? W : 64;
+                int32_t* sg_own = w.seg;
                 int32_t* sg_h0 = sg_own + kSeg;
                 int32_t* sg_len = sg_h0 + kSeg;
-                int32_t* sg_pre = sh.segpre + wave * (kSeg + 1);
+                int32_t* sg_pre = w.segpre;
                 // accepted hits are compacted in hit order, and the flattened hits
                 // run owner by owner, so each owner's accepted hits of a round form
                 // one range [ac_first, ac_last]
-                int32_t* ac_first = sh.acc + wave * 3 * kAcc;
+                int32_t* ac_first = w.acc;
                 int32_t* ac_last = ac_first + 64;
                 int32_t* ac_id = ac_first + kAcc;
                 int32_t* ac_bi = ac_id + kAcc;
-                float* ac_c2 = sh.accc2 + wave * kAcc;
+                float* ac_c2 = w.accc2;
                 // wave-wide exclusive prefix sum (and total) of one int per lane
                 auto wave_scan = [&](int v, int* total) {
                     int incl = v;
@@ -982,7 +978,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
                 int R = 0;
                 const int rpre = wave_scan(nrow, &R);
                 // the row parameters of each owner, for the lanes that expand its rows
-                int32_t* rw_par = sh.rowp + wave * 5 * 64;
+                int32_t* rw_par = w.rowp;
                 rw_par[ln] = rpre;
                 rw_par[64 + ln] = row_lo;
                 rw_par[128 + ln] = v0 | (v1 << 16);
@@ -1079,10 +1075,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
                             float c2f = 0.0f;
                             const int o = own[q];
                             if (o >= 0) {
-                                const int ot = (wave << 6) + o;
                                 const float hcp = r1[q].y, hsp = r1[q].z;
-                                const float4 oa = *(const float4*)&sh.orec[ot * 8];
-                                const float4 ob = *(const float4*)&sh.orec[ot * 8 + 4];
+                                const float4 oa = *(const float4*)&w.orec[o * 8];
+                                const float4 ob = *(const float4*)&w.orec[o * 8 + 4];
                                 const T ox = T(oa.x), oy = T(oa.y), oz = T(oa.z);
                                 const T cpp = T(oa.w), spp = T(ob.x);
                                 const T sin_dphi = T(ob.y), wv = T(ob.z);
@@ -1108,7 +1103,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
                                     f.vu = U(r0[q].w) * U(r0[q].w);
                                     f.vv = U(r1[q].x) * U(r1[q].x);
                                     C pc[6];
-                                    load_owner_cov(sh.ocov + ot * kOwnCov<C>, pc);
+                                    load_owner_cov(w.ocov + o * kOwnCov<C>, pc);
                                     const U c2u = hit_chi2_pos<U>(U(ox), U(oy), U(oz), U(pc[0]), U(pc[1]),
                                                                   U(pc[2]), U(pc[3]), U(pc[4]), U(pc[5]),
                                                                   f, kind);
@@ -1191,105 +1186,110 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
                     wave_fence();
                 }
             }
-            // ---- publish this lane's step outcome and children
-            if (lane_ok) {
-                sh.meta[0 * W + t] = nhits;
-                sh.meta[1 * W + t] = misses;
-                sh.meta[2 * W + t] = (int32_t)status;
-                sh.meta[3 * W + t] = (done ? 1 : 0) | ((pl + 1) << 8) | (pos << 16);
-                const int nk = nacc < MC ? nacc : MC;
-                sh.nchild[t] = occupied ? nk : -1;
+            // ---- a5: per-seed selection.  The candidates of a seed write their
+            // children's merge keys (all different) into one list in LDS: each its
+            // accepted hits, best first, and the child without a hit.  The seed's
+            // lanes then take the list's keys in turn, and a key's rank is the
+            // number of smaller ones in the list; ranks below max_cands survive.
+            // (One lane merging its seed's sorted lists waited on LDS for every
+            // pick: 2.4 us of a median step's 18; every lane comparing its own
+            // keys with all places of the other lanes' lists took 3.3, most
+            // places being empty.)
+            const int nk = nacc < MC ? nacc : MC;       // hit children
+            wave_fence();                               // the scan's LDS is free
+            if (lane_ok) w.sel[s_loc * MC + slot] = ~0ull;
+            int n_key, n_key_max;      // the seed's keys, and the most of any seed of the wave
+            {
+                // where this candidate's keys start: the counts (at most
+                // kMaxCands + 1, so four bits) of the seed's lower slots
+                const int cnt = occupied ? nk + 1 : 0;
+                const uint64_t lower = lane_ok ? ((1ull << slot) - 1) << lbase : 0;
+                const uint64_t mine = lane_ok ? ((1ull << MC) - 1) << lbase : 0;
+                int at = 0;
+                n_key = 0;
 #pragma unroll
-                for (int k = 0; k < kMaxCands; ++k) {
-                    sh.cchi2[k * W + t] = lk[k] == ~0ull ? 3.0e38f : child_key_chi2(lk[k]);
-                    sh.cbidx[k * W + t] = lbi[k];
+                for (int b = 0; b < 4; ++b) {
+                    const uint64_t m = __ballot((cnt >> b) & 1);
+                    at += __popcll(m & lower) << b;
+                    n_key += __popcll(m & mine) << b;
                 }
-            }
-            __syncthreads();
-            // ---- a5: per-seed selection (k-way merge of per-parent sorted children)
-            // by the seed's slot-0 lane, the parents' list heads held in
-            // registers: one LDS read per pick after the initial loads
-            if (valid && slot == 0) {
-                const int base = lbase;
-                // list heads as merge keys; parents fill slots 0, 1, ...: the
-                // first empty slot ends them
-                uint64_t K[kMaxCands];
-                bool stop = false;
+                n_key_max = 0;
+                while (__ballot(n_key > n_key_max)) n_key_max += 4;
+                uint64_t* keys = w.key + s_loc * MC * (MC + 1);
+                if (occupied) {
 #pragma unroll
-                for (int j = 0; j < kMaxCands; ++j) {
-                    const int nkj = j < MC ? sh.nchild[base + j] : -1;
-                    stop = stop || nkj < 0;
-                    K[j] = ~0ull;
-                    if (!stop) {
-                        // head: the best child (nk == 0: the child without a hit)
-                        const int nh = sh.meta[0 * W + base + j];
-                        const float c0 = sh.pchi2[base + j];
-                        K[j] = nkj > 0 ? merge_key(nh + 1, c0 + sh.cchi2[0 * W + base + j], j, 0)
-                                       : merge_key(nh, c0, j, 0);
+                    for (int c = 0; c < kMaxCands; ++c)
+                        if (c < nk) {
+                            keys[at + c] = merge_key(nhits + 1, chi2 + child_key_chi2(lk[c]), slot, c);
+                            w.cbidx[c * 64 + ln64] = lbi[c];
+                        }
+                    keys[at + nk] = merge_key(nhits, chi2, slot, nk);
+                }
+                wave_fence();
+                constexpr int kOwn = 3;                 // keys a lane ranks at once
+                for (int i0 = slot; __ballot(lane_ok && i0 < n_key); i0 += kOwn * MC) {
+                    uint64_t own[kOwn];
+                    int rank[kOwn];
+#pragma unroll
+                    for (int u = 0; u < kOwn; ++u) {
+                        const int i = i0 + u * MC;
+                        own[u] = lane_ok && i < n_key ? keys[i] : 0ull;
+                        rank[u] = 0;
                     }
-                }
-                int nsel = 0;
-                for (int r = 0; r < MC; ++r) {
-                    uint64_t best = K[0];
+                    for (int j = 0; j < n_key_max; j += 4) {
+                        uint64_t k2[4];
 #pragma unroll
-                    for (int j = 1; j < kMaxCands; ++j) best = K[j] < best ? K[j] : best;
-                    if (best == ~0ull) break;
-                    const int bj = (int)(best >> 16) & 0xFF, c = (int)(best >> 8) & 0xFF;
-                    sh.sel[(s_loc * kMaxCands + r) * 2 + 0] = (int8_t)bj;
-                    sh.sel[(s_loc * kMaxCands + r) * 2 + 1] = (int8_t)c;
-                    ++nsel;
-                    // advance the winner's list: its next hit child, then the
-                    // child without a hit, then nothing
-                    const int tj = base + bj, cn = c + 1;
-                    const int n = sh.nchild[tj], h0 = sh.meta[0 * W + tj];
-                    const float cc0 = sh.pchi2[tj];
-                    const float cx = sh.cchi2[(cn < kMaxCands ? cn : kMaxCands - 1) * W + tj];
-                    const uint64_t nkey = cn < n    ? merge_key(h0 + 1, cc0 + cx, bj, cn)
-                                          : cn == n ? merge_key(h0, cc0, bj, cn)
-                                                    : ~0ull;
+                        for (int v = 0; v < 4; ++v) k2[v] = j + v < n_key ? keys[j + v] : ~0ull;
 #pragma unroll
-                    for (int j = 0; j < kMaxCands; ++j) K[j] = j == bj ? nkey : K[j];
+                        for (int v = 0; v < 4; ++v)
+#pragma unroll
+                            for (int u = 0; u < kOwn; ++u) rank[u] += k2[v] < own[u] ? 1 : 0;
+                    }
+#pragma unroll
+                    for (int u = 0; u < kOwn; ++u)
+                        if (lane_ok && i0 + u * MC < n_key && rank[u] < MC) w.sel[s_loc * MC + rank[u]] = own[u];
                 }
-                sh.nsel[s_loc] = nsel;
             }
-            __syncthreads();
+            wave_fence();
             // ---- a6: materialise the surviving children (Kalman update for hit
             // children).  A child copies its parent's predicted state from the
             // parent's registers (same wave); every lane takes part in the copy.
             int sel_j = 0, sel_c = 0, src = ln64;
             bool occ_new = false;
+            uint64_t sel_key = ~0ull;
             if (valid) {
-                occ_new = slot < sh.nsel[s_loc];
+                sel_key = w.sel[s_loc * MC + slot];
+                occ_new = sel_key != ~0ull;
                 if (occ_new) {
-                    sel_j = sh.sel[(s_loc * kMaxCands + slot) * 2 + 0];
-                    sel_c = sh.sel[(s_loc * kMaxCands + slot) * 2 + 1];
-                    src = (lbase + sel_j) & 63;
+                    sel_j = (int)(sel_key >> 16) & 0xFF;
+                    sel_c = (int)(sel_key >> 8) & 0xFF;
+                    src = lbase + sel_j;
                 }
             }
 #pragma unroll
             for (int k = 0; k < 6; ++k) p[k] = __shfl(p[k], src);
 #pragma unroll
             for (int k = 0; k < 21; ++k) P[k] = __shfl(P[k], src);
+            nhits = __shfl(nhits, src);
+            misses = __shfl(misses, src);
+            status = __shfl(status, src);
+            // the parent's outcome: done, its layer + 1, its hit children, its plan position
+            const int m3 = __shfl((done ? 1 : 0) | ((pl + 1) << 1) | (nk << 8) | (pos << 16), src);
             if (valid) {
                 occupied = occ_new;
                 int2 bpe = make_int2(-1, 0xFF00);
                 if (occupied) {
                     const int j = sel_j;
                     const int c = sel_c;
-                    const int tj = lbase + j;
-                    chi2 = sh.pchi2[tj];
-                    nhits = sh.meta[0 * W + tj];
-                    misses = sh.meta[1 * W + tj];
-                    status = (uint32_t)sh.meta[2 * W + tj];
-                    const int m3 = sh.meta[3 * W + tj];
+                    // the child's chi2, with its hit's where it has one
+                    chi2 = merge_key_chi2(sel_key);
                     done = (m3 & 1) != 0;
-                    const int ppl = ((m3 >> 8) & 0xFF) - 1;
+                    const int ppl = ((m3 >> 1) & 0x7F) - 1;
                     if constexpr (STEER) pos = (m3 >> 16) & 0xFF;
-                    const int nk = sh.nchild[tj];
                     if (ppl >= 0) {
                         ++n_kept;
-                        if (c < nk) {
-                            const int bi = sh.cbidx[c * W + tj];
+                        if (c < ((m3 >> 8) & 0xFF)) {
+                            const int bi = w.cbidx[c * 64 + lbase + j];
                             const BinnedHit hh = a.bh[bi];
                             HitFrame<U> f;
                             f.hx = U(hh.x);
@@ -1300,13 +1300,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
                             f.vu = U(hh.su) * U(hh.su);
                             f.vv = U(hh.sv) * U(hh.sv);
                             U c2 = U(0);
-                            const int r = kf_update<T, C, U>(p, P, f, sh.layers[ppl].kind, &c2);
+                            const int r = kf_update<T, C, U>(p, P, f, layers[ppl].kind, &c2);
                             ++n_upd;
                             if (r) {
                                 status |= (uint32_t)r;
                                 done = true;
                             }
-                            chi2 = chi2 + sh.cchi2[c * W + tj];
                             nhits += 1;
                             misses = 0;
                             bpe = make_int2(hh.idx, j | (ppl << 8));
@@ -1321,30 +1320,64 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
                     bp_base[((size_t)step * S + s_loc) * kMaxCands + slot] = bpe;
                 }
             }
+            // (the next step's LDS writes come after every lane's reads above)
+            wave_fence();
             ++nsteps;
         }
-        // ---- a7: best candidate (slot 0, candidates are kept sorted) and its hit list
-        if (valid && slot == 0) {
-            const int64_t ol = a.n_layers;
-            int32_t* oh = a.out_hits + (int64_t)sid * ol;
-            // a layer visited more than once (a looper curling back) reports its
-            // latest hit: walk the back-pointers from the last step and keep the
-            // first hit met per layer, then the seed hits where nothing came later
-            for (int l = 0; l < nl; ++l) oh[l] = -1;
-            int k = 0;
-            for (int st = nsteps - 1; st >= 0; --st) {
-                const int2 e = bp_base[((size_t)st * S + s_loc) * kMaxCands + k];
-                const int lay = (e.y >> 8) & 0xFF;
-                if (e.x >= 0 && lay < nl && oh[lay] < 0) oh[lay] = e.x;
-                k = e.y & 0xFF;
+        // ---- a7: best candidate (slot 0, candidates are kept sorted) and its hit list.
+        // A layer visited more than once (a looper curling back) reports its
+        // latest hit: the back-pointers are walked from the last step and the
+        // first hit met per layer is kept, then the seed hits where nothing came
+        // later.  Each lane loads the entries that its own slot wrote, several
+        // steps at once, and the walk follows the chain by shuffles; the layers
+        // already filled are a bit mask.  (One lane chasing the entries and the
+        // filled layers through memory took about 25 us a tile.)
+        {
+            int32_t* oh = a.out_hits + (int64_t)sid * nl;
+            if (valid)
+                for (int l = slot; l < nl; l += MC) oh[l] = -1;
+            int32_t sh_hit[3], sh_lay[3];
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                sh_hit[q] = valid ? a.seed_hits[q * a.sld + sid] : -1;
+                const bool in = sh_hit[q] >= 0 && sh_hit[q] < a.n_hits;
+                sh_lay[q] = in ? a.hit_layer[sh_hit[q]] : -1;
             }
-            for (int q = 2; q >= 0; --q) {
-                const int hi = a.seed_hits[q * a.sld + sid];
-                if (hi >= 0 && hi < a.n_hits) {
-                    const int hl = a.hit_layer[hi];
-                    if (hl >= 0 && hl < nl && oh[hl] < 0) oh[hl] = hi;
+            wave_fence();                       // the -1s come before the hits
+            uint64_t seen = 0;
+            int k = 0;
+            constexpr int kWalk = 4;            // steps loaded at once
+            for (int s1 = nsteps; s1 > 0; s1 -= kWalk) {
+                int2 e[kWalk];
+#pragma unroll
+                for (int u = 0; u < kWalk; ++u) {
+                    const int st = s1 - 1 - u;
+                    e[u] = make_int2(-1, 0xFF00);
+                    if (valid && st >= 0) e[u] = bp_base[((size_t)st * S + s_loc) * kMaxCands + slot];
+                }
+#pragma unroll
+                for (int u = 0; u < kWalk; ++u) {
+                    if (s1 - 1 - u < 0) break;
+                    const int from = lbase + k;
+                    const int ex = __shfl(e[u].x, from), ey = __shfl(e[u].y, from);
+                    const int lay = (ey >> 8) & 0xFF;
+                    if (valid && ex >= 0 && lay < nl && !((seen >> lay) & 1)) {
+                        seen |= 1ull << lay;
+                        if (slot == 0) oh[lay] = ex;
+                    }
+                    k = ey & 0xFF;
                 }
             }
+#pragma unroll
+            for (int q = 2; q >= 0; --q) {
+                const int hl = sh_lay[q];
+                if (valid && hl >= 0 && hl < nl && !((seen >> hl) & 1)) {
+                    seen |= 1ull << hl;
+                    if (slot == 0) oh[hl] = sh_hit[q];
+                }
+            }
+        }
+        if (valid && slot == 0) {
 #pragma unroll
             for (int q = 0; q < 6; ++q) a.opar[q * a.old + sid] = float(p[q]);
 #pragma unroll
@@ -1355,16 +1388,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
         }
     }
     if (a.counters) {
-        // wave-level reduction of the per-lane counts, one atomic per wave
+        // wave-level reduction of the per-lane counts, added by one atomic
+        // instruction of eight lanes (their counters share a line)
         unsigned long long c[kFindCounters] = {(unsigned long long)n_prop, (unsigned long long)n_upd,
                                                (unsigned long long)n_chi2, (unsigned long long)n_newton,
                                                (unsigned long long)n_disk, (unsigned long long)n_guess,
                                                (unsigned long long)n_fallback, (unsigned long long)n_kept};
+        unsigned long long mine = 0;
 #pragma unroll
         for (int q = 0; q < kFindCounters; ++q) {
             for (int o = 32; o > 0; o >>= 1) c[q] += __shfl_xor(c[q], o);
-            if ((t & 63) == 0) atomicAdd(&a.counters[q], c[q]);
+            if (ln64 == q) mine = c[q];
         }
+        if (ln64 < kFindCounters && mine) atomicAdd(&a.counters[ln64], mine);
     }
 }
 
@@ -1373,9 +1409,9 @@ namespace {
 inline unsigned blocks_for(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 }
 
-size_t find_shared_size(int W, int S, int nl, int prec)
+size_t find_shared_size(int W, int nl, int prec)
 {
-    return find_shared_bytes(W, S, nl, prec == KF_PREC_FP32 ? sizeof(float) : sizeof(double));
+    return prec == KF_PREC_FP32 ? find_shared_bytes<float>(W, nl) : find_shared_bytes<double>(W, nl);
 }
 
 // Instantiations: (precision) x (plain, learned, steered; each also in the
@@ -1406,10 +1442,10 @@ static hipError_t find_occ(bool mat, bool steer, bool field, int W, size_t lds, 
                : find_occ2<T, C, U, LEARN, false>(steer, field, W, lds, out);
 }
 
-hipError_t find_max_blocks_per_cu(int W, int S, int nl, int prec, bool learn, bool mat, bool steer,
+hipError_t find_max_blocks_per_cu(int W, int nl, int prec, bool learn, bool mat, bool steer,
                                   bool field, int* out)
 {
-    const size_t lds = find_shared_size(W, S, nl, prec);
+    const size_t lds = find_shared_size(W, nl, prec);
     if (prec == KF_PREC_FP32)
         return learn ? find_occ<float, float, float, true>(mat, steer, field, W, lds, out)
                      : find_occ<float, float, float, false>(mat, steer, field, W, lds, out);
@@ -1801,7 +1837,7 @@ hipError_t launch_dedup(const FindPlan& pl, int64_t n, int nl, const int32_t* ro
 }
 
 size_t plan_find(FindPlan* pl, void* base, int64_t n_hits, int n_events, int64_t n_seeds,
-                 int n_layers, int grid, int seeds_per_tile)
+                 int n_layers, int n_waves, int seeds_per_tile)
 {
     size_t off = 0;
     auto take = [&](size_t bytes) -> void* {
@@ -1841,8 +1877,8 @@ size_t plan_find(FindPlan* pl, void* base, int64_t n_hits, int n_events, int64_t
     }
     pl->queue_loopers = (int32_t*)take(sizeof(int32_t) * kQueues);
     pl->bsum = (int32_t*)take(sizeof(int32_t) * nsum);
-    pl->bp = (int2*)take(sizeof(int2) * (size_t)grid * n_layers * seeds_per_tile * kMaxCands);
-    pl->tile_counter = (int32_t*)take(sizeof(int32_t) * 64);
+    pl->bp = (int2*)take(sizeof(int2) * (size_t)n_waves * n_layers * seeds_per_tile * kMaxCands);
+    pl->tile_counter = (int32_t*)take(sizeof(int32_t) * kQueues * kQueueStride);
     pl->clean_best = (unsigned long long*)take(sizeof(unsigned long long) * nh);
     pl->clean_rec = (CleanRec*)take(sizeof(CleanRec) * ns);
     pl->dup_cnt = (int32_t*)take(sizeof(int32_t) * (nh + 1));
@@ -1883,7 +1919,7 @@ static void find_launch(const FindArgs& a, int W, int grid, size_t lds, hipStrea
 
 hipError_t launch_find_kernel(const FindArgs& a, int W, int grid, int prec, bool learn, hipStream_t s)
 {
-    const size_t lds = find_shared_size(W, a.seeds_per_tile, a.n_layers, prec);
+    const size_t lds = find_shared_size(W, a.n_layers, prec);
     if (prec == KF_PREC_FP32)
         learn ? find_launch<float, float, float, true>(a, W, grid, lds, s)
               : find_launch<float, float, float, false>(a, W, grid, lds, s);

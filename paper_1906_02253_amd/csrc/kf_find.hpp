@@ -8,14 +8,12 @@ namespace kfmi {
 constexpr int kMaxCands = 8;    // candidate slots per seed the kernel is built for
 constexpr int kMaxLayerBins = 16384;   // nbin_phi * nbin_2 of one layer (LDS histogram)
 constexpr int kFindCounters = 8;       // event counters of a finding call
+constexpr int kQueues = 8;             // tile queues of the finding kernel, one per XCD
+constexpr int kQueueStride = 32;       // their counters, a 128-byte line apart
 
-// Seeds per workgroup of the finding kernel: max_cands lanes per seed, and a
+// Seeds a wave of the finding kernel holds: max_cands lanes per seed, and a
 // seed never straddles two waves (its candidates exchange state by shuffles).
 __host__ __device__ inline int seeds_per_wave(int W, int MC) { return (W < 64 ? W : 64) / MC; }
-__host__ __device__ inline int seeds_per_wg(int W, int MC)
-{
-    return W < 64 ? W / MC : (W / 64) * (64 / MC);
-}
 
 // One binned hit: position, sigmas, azimuth cos/sin and the caller's hit index.
 struct alignas(16) BinnedHit {
@@ -58,8 +56,8 @@ struct FindArgs {
     int32_t* ondf;
     uint32_t* ostatus;
     // scratch
-    int2* bp;                     // per workgroup: [n_layers][S][kMaxCands] back-pointers
-    int32_t* tile_counter;
+    int2* bp;                     // per wave: [n_layers][seeds_per_tile][kMaxCands] back-pointers
+    int32_t* tile_counter;        // [kQueues * kQueueStride]
     const int32_t* queue_loopers; // [kQueues] costliest-class seeds at the head of each tile
                                   // queue's range (served in sparser tiles)
     unsigned long long* counters; // optional [kFindCounters]: propagations, updates, chi2 tests,
@@ -71,7 +69,7 @@ struct FindArgs {
     kf_params prm;
     int material;
     int n_tiles;
-    int seeds_per_tile;
+    int seeds_per_tile;           // at most seeds_per_wave
     MatMap mat;                   // r-z material map (x0 == nullptr: none)
     const SteerDev* steer;        // tracking regions and plans (nullptr: dynamic navigation)
     MlpDev mlp;                   // learned guess (KF_INIT_MLP)
@@ -118,9 +116,9 @@ struct FindPlan {
 
 // Lays out the scratch of a call from `base` (nullptr: only sizes it); returns bytes.
 size_t plan_find(FindPlan* pl, void* base, int64_t n_hits, int n_events, int64_t n_seeds,
-                 int n_layers, int grid, int seeds_per_tile);
-size_t find_shared_size(int W, int S, int nl, int prec);
-hipError_t find_max_blocks_per_cu(int W, int S, int nl, int prec, bool learn, bool mat, bool steer,
+                 int n_layers, int n_waves, int seeds_per_tile);
+size_t find_shared_size(int W, int nl, int prec);
+hipError_t find_max_blocks_per_cu(int W, int nl, int prec, bool learn, bool mat, bool steer,
                                   bool field, int* out);
 hipError_t launch_scan(const int32_t* in, int32_t* out, int64_t n, int32_t* bsum, hipStream_t s);
 hipError_t launch_fill(int32_t* p, int64_t n, int32_t v, hipStream_t s);

@@ -13,24 +13,57 @@ namespace kfmi {
 // par and cov are stored in T, the state precision (FP32 in the mixed and
 // FP32 modes); in registers the state is held in U (the update precision) and
 // the covariance in C (the covariance-arithmetic precision).
-template <typename T, typename C, typename U>
-__device__ inline void load_state(const T* par, const T* cov, int64_t ld, int64_t i, U p[6],
-                                  C P[21])
+// A workgroup's elements start at b0 and lane i takes element b0 + i.  The row
+// stride is made opaque at each use, so that the compiler steps one scalar
+// address from row to row there instead of keeping all 27 rows' addresses in
+// 54 vector registers from the load to the store.
+__device__ inline int64_t opaque(int64_t v)
 {
-#pragma unroll
-    for (int k = 0; k < 6; ++k) p[k] = U(par[k * ld + i]);
-#pragma unroll
-    for (int k = 0; k < 21; ++k) P[k] = C(cov[k * ld + i]);
+    asm volatile("" : "+s"(v));
+    return v;
 }
 
 template <typename T, typename C, typename U>
-__device__ inline void store_state(T* par, T* cov, int64_t ld, int64_t i, const U p[6],
+__device__ inline void load_state(const T* par, const T* cov, int64_t ld, int64_t b0, unsigned i, U p[6],
+                                  C P[21])
+{
+    const int64_t row = opaque(ld);
+    const T* q = par + b0;
+#pragma unroll
+    for (int k = 0; k < 6; ++k, q += row) p[k] = U(q[i]);
+    q = cov + b0;
+#pragma unroll
+    for (int k = 0; k < 21; ++k, q += row) P[k] = C(q[i]);
+    poison_nonfinite(P);
+}
+
+template <typename T, typename C, typename U>
+__device__ inline void store_state(T* par, T* cov, int64_t ld, int64_t b0, unsigned i, const U p[6],
                                    const C P[21])
 {
+    const int64_t row = opaque(ld);
+    T* q = par + b0;
 #pragma unroll
-    for (int k = 0; k < 6; ++k) par[k * ld + i] = T(p[k]);
+    for (int k = 0; k < 6; ++k, q += row) q[i] = T(p[k]);
+    q = cov + b0;
 #pragma unroll
-    for (int k = 0; k < 21; ++k) cov[k * ld + i] = T(P[k]);
+    for (int k = 0; k < 21; ++k, q += row) q[i] = T(P[k]);
+}
+
+// A layer as propagate_to reads it.
+template <typename T>
+struct StepLayer {
+    int32_t kind;
+    T r_or_z, x0;
+};
+
+// The layers' StepLayers in LDS; every thread of the workgroup calls it.
+template <typename T>
+__device__ inline void stage_layers(const kf_layer* layers, int n_layers, StepLayer<T>* out)
+{
+    for (int l = threadIdx.x; l < n_layers; l += blockDim.x)
+        out[l] = StepLayer<T>{layers[l].kind, T(layers[l].r_or_z), T(layers[l].x0)};
+    __syncthreads();
 }
 
 // Propagate (p, P) to layer L.  The surface solve, the helix and the
@@ -43,7 +76,7 @@ __device__ inline void store_state(T* par, T* cov, int64_t ld, int64_t i, const 
 // map.  Both are compile-time variants so that the uniform-field, per-layer
 // material instantiation keeps its register budget.
 template <typename T, typename C, typename U, bool FIELD, bool MAT>
-__device__ inline int propagate_to(U p[6], C P[21], const kf_layer& L, const kf_params& prm,
+__device__ inline int propagate_to(U p[6], C P[21], const StepLayer<T>& L, const kf_params& prm,
                                    bool material, const MatMap& mat, T s_init, T* s_out, int* evals,
                                    int* fallbacks)
 {
@@ -83,30 +116,27 @@ __device__ inline int propagate_to(U p[6], C P[21], const kf_layer& L, const kf_
         for (int k = 0; k < 6; ++k) fin &= isfinite(p[k]);
         return fin ? 0 : KF_ST_NAN;
     }
+    T st_, ct_;
+    Tr<T>::sincos_(pt[5], &st_, &ct_);
     if (L.kind == 0) {
         const T h = -kb * pt[3];
         T sph, cph;
         Tr<T>::sincos_(pt[4], &sph, &cph);
-        const T r_l = T(L.r_or_z);
-        T s_hi;
-        if (!barrel_bracket(pt[0], pt[1], cph, sph, h, r_l, &s_hi)) return KF_ST_UNREACHABLE;
-        int st = solve_barrel(pt, h, cph, sph, r_l, s_hi, prm, s_init, prm.mlp_max_iter, &s, evals,
+        int st = reach_barrel(pt, h, cph, sph, T(L.r_or_z), prm, s_init, prm.mlp_max_iter, &s, evals,
                               fallbacks);
         if (st) return st;
     } else {
-        T st_, ct_;
-        Tr<T>::sincos_(pt[5], &st_, &ct_);
         if (ct_ == T(0)) return KF_ST_UNREACHABLE;
         s = (T(L.r_or_z) - pt[2]) * st_ / ct_;
         *evals += 1;
         if (s < T(0)) return KF_ST_UNREACHABLE;
     }
-    transport(p, P, s, kb, L.kind, T(L.r_or_z));
+    transport(p, P, s, kb, L.kind, T(L.r_or_z), st_, ct_);
     if (material) {
         if constexpr (MAT)
             add_material(p, P, L, mat, T(prm.mass));
         else
-            add_scatter(p, P, L.kind, T(L.x0), T(prm.mass));
+            add_scatter(p, P, L.kind, T(L.x0), T(prm.mass), st_, ct_);
     }
     if (s_out) *s_out = s;
     bool fin = true;
@@ -126,7 +156,7 @@ __global__ __launch_bounds__(256) void seed_kernel(int64_t n, int64_t ld, int64_
                                                    T* __restrict__ chi2, int32_t* __restrict__ ndf,
                                                    uint32_t* __restrict__ status)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t b0 = (int64_t)blockIdx.x * blockDim.x, i = b0 + threadIdx.x;
     if (i >= n) return;
     const int32_t a = seed_hits[i], b = seed_hits[ld + i], c = seed_hits[2 * ld + i];
     if (a < 0 || b < 0 || c < 0 || a >= n_hits || b >= n_hits || c >= n_hits) {
@@ -165,7 +195,7 @@ __global__ __launch_bounds__(256) void seed_kernel(int64_t n, int64_t ld, int64_
     P[pk(0, 0)] = P[pk(1, 1)] = P[pk(2, 2)] = T(1);
     P[pk(3, 3)] = T(4);
     P[pk(4, 4)] = P[pk(5, 5)] = T(0.01);
-    store_state<T, T, T>(par, cov, ld, i, p, P);
+    store_state<T, T, T>(par, cov, ld, b0, threadIdx.x, p, P);
     chi2[i] = T(0);
     ndf[i] = -5;
     status[i] = 0;
@@ -184,7 +214,9 @@ __global__ __launch_bounds__(256) void propagate_kernel(int64_t n, int64_t ld, T
                                                         MatMap mat, float* __restrict__ path_len,
                                                         int32_t* __restrict__ iters, MlpDev mlp)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ StepLayer<T> sl[kMaxLayers];
+    stage_layers(layers, n_layers, sl);
+    const int64_t b0 = (int64_t)blockIdx.x * blockDim.x, i = b0 + threadIdx.x;
     if (!LEARN && i >= n) return;
     const bool inb = i < n;
     const int32_t l = inb ? target[i] : -1;
@@ -199,10 +231,10 @@ __global__ __launch_bounds__(256) void propagate_kernel(int64_t n, int64_t ld, T
     }
     U p[6];
     C P[21];
-    kf_layer L;
+    StepLayer<T> L{};
     if (active) {
-        load_state(par, cov, ld, i, p, P);
-        L = layers[l];
+        load_state(par, cov, ld, b0, threadIdx.x, p, P);
+        L = sl[l];
     }
     T s_init = T(-1);
     if (LEARN) {
@@ -232,7 +264,7 @@ __global__ __launch_bounds__(256) void propagate_kernel(int64_t n, int64_t ld, T
     if (r) {
         st |= (uint32_t)r;
     } else {
-        store_state(par, cov, ld, i, p, P);
+        store_state(par, cov, ld, b0, threadIdx.x, p, P);
     }
     status[i] = st;
     if (path_len) path_len[i] = float(s);
@@ -259,35 +291,75 @@ struct FitArgs {
     MlpDev mlp;                  // learned guess (KF_INIT_MLP)
 };
 
+// What a step reads besides the state: its layer and hit index, and the hit.
+struct FitIndex {
+    int32_t l, hi;
+};
+struct FitHit {
+    float x, y, z, su, sv;
+};
+
 // Steps [k0, k1) of the fit.  init: start a fresh fit (chi2 = 0, ndf = -5).
 // LEARN: every lane of the wave walks all steps (finished lanes idle), so
 // that the network call at each step is in uniform control flow.
+// The loads run ahead of the arithmetic: while step k is computed, the hit of
+// step k + 1 and the indices of step k + 2 are on their way, so that a step
+// waits for neither of its two dependent loads.
 template <typename T, typename C, typename U, bool LEARN, bool FIELD, bool MAT>
-__global__ __launch_bounds__(256) void fit_kernel(FitArgs a, int k0, int k1, int init)
+__global__ __launch_bounds__(256, 2) void fit_kernel(FitArgs a, int k0, int k1, int init)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (!LEARN && i >= a.n) return;
-    const bool inb = i < a.n;
+    __shared__ StepLayer<T> sl[kMaxLayers];
+    stage_layers(a.layers, a.n_layers, sl);
+    const int64_t b0 = (int64_t)blockIdx.x * blockDim.x;
+    const unsigned i = threadIdx.x;
+    if (!LEARN && b0 + i >= a.n) return;
+    const bool inb = b0 + i < a.n;
     const int64_t ld = a.ld;
     T* par = (T*)a.par;
     T* cov = (T*)a.cov;
-    T* chi2p = (T*)a.chi2;
-    uint32_t st = (init || !inb) ? 0u : a.status[i];
-    int32_t ndf = (init || !inb) ? -5 : a.ndf[i];
+    T* chi2p = (T*)a.chi2 + b0;
+    uint32_t* stp = a.status + b0;
+    int32_t* ndfp = a.ndf + b0;
+    uint32_t st = (init || !inb) ? 0u : stp[i];
+    int32_t ndf = (init || !inb) ? -5 : ndfp[i];
     U chi2 = (init || !inb) ? U(0) : U(chi2p[i]);
     bool alive = inb && !(st & kFreezeMask);
     if (!LEARN && !alive) return;
     const bool was_alive = alive;
+    auto load_index = [&](int k) {
+        FitIndex x{-1, -1};
+        if (alive && k < k1) {
+            x.l = a.layer_seq ? (a.layer_seq + (k * ld + b0))[i] : k;
+            x.hi = (a.hit_idx + (k * ld + b0))[i];
+        }
+        return x;
+    };
+    auto load_hit = [&](const FitIndex& x) {
+        FitHit h{};
+        if (x.l >= 0 && x.hi >= 0 && x.hi < a.n_hits) {
+            h.x = a.hx[x.hi];
+            h.y = a.hy[x.hi];
+            h.z = a.hz[x.hi];
+            h.su = a.hsu[x.hi];
+            h.sv = a.hsv[x.hi];
+        }
+        return h;
+    };
+    FitIndex now = load_index(k0), next = load_index(k0 + 1);
     // the state stays in U between steps (rounded to T only when stored)
     U p[6];
     C P[21];
-    if (alive) load_state(par, cov, ld, i, p, P);
+    if (alive) load_state(par, cov, ld, b0, i, p, P);
+    FitHit hit = load_hit(now);
     bool touched = false;
     for (int k = k0; k < k1; ++k) {
         if (!LEARN && !alive) break;
-        int32_t l = -1;
+        const int32_t l = now.l, hi = now.hi;
+        const FitHit h = hit;
+        now = next;
+        hit = load_hit(next);
+        next = load_index(k + 2);
         if (alive) {
-            l = a.layer_seq ? a.layer_seq[(int64_t)k * ld + i] : k;
             if (l < 0) {
                 alive = false;
             } else if (l >= a.n_layers) {
@@ -295,8 +367,8 @@ __global__ __launch_bounds__(256) void fit_kernel(FitArgs a, int k0, int k1, int
                 alive = false;
             }
         }
-        kf_layer L;
-        if (alive) L = a.layers[l];
+        StepLayer<T> L{};
+        if (alive) L = sl[l];
         T s_init = T(-1);
         if (LEARN) {
             float f[kMlpIn] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -312,19 +384,6 @@ __global__ __launch_bounds__(256) void fit_kernel(FitArgs a, int k0, int k1, int
             if (want) s_init = T(mlp_guess(f, y));
         }
         if (!alive) continue;
-        // the step's hit is read before the propagation, so that its two
-        // dependent loads (index, then coordinates) overlap the state's loads
-        // and the transport instead of following them
-        const int32_t hi = a.hit_idx[(int64_t)k * ld + i];
-        const bool has_hit = hi >= 0 && hi < a.n_hits;
-        float hx = 0.f, hy = 0.f, hz = 0.f, hsu = 0.f, hsv = 0.f;
-        if (has_hit) {
-            hx = a.hx[hi];
-            hy = a.hy[hi];
-            hz = a.hz[hi];
-            hsu = a.hsu[hi];
-            hsv = a.hsv[hi];
-        }
         int ev = 0, fb = 0;
         int r = propagate_to<T, C, U, FIELD, MAT>(p, P, L, a.prm, a.material != 0, a.mat, s_init,
                                                    (T*)nullptr, &ev, &fb);
@@ -340,8 +399,8 @@ __global__ __launch_bounds__(256) void fit_kernel(FitArgs a, int k0, int k1, int
             alive = false;
             continue;
         }
-        if (has_hit) {
-            HitFrame<U> f = hit_frame<U>(hx, hy, hz, hsu, hsv);
+        if (hi >= 0) {
+            HitFrame<U> f = hit_frame<U>(h.x, h.y, h.z, h.su, h.sv);
             U c2 = U(0);
             r = kf_update<U, C, U>(p, P, f, L.kind, &c2);
             if (r) {
@@ -358,10 +417,10 @@ __global__ __launch_bounds__(256) void fit_kernel(FitArgs a, int k0, int k1, int
     if (!was_alive) return;
     // on failure the registers hold the last good state (a failed solve or
     // update leaves them untouched)
-    if (touched) store_state(par, cov, ld, i, p, P);
+    if (touched) store_state(par, cov, ld, b0, i, p, P);
     chi2p[i] = T(chi2);
-    a.ndf[i] = ndf;
-    a.status[i] = st;
+    ndfp[i] = ndf;
+    stp[i] = st;
 }
 
 // ---------------------------------------------------------------- launchers

@@ -182,20 +182,160 @@ KF_HD inline int newton_barrel(T x, T y, T phi, T h, T r_l, T s, T s_lo, T s_hi,
     return KF_ST_NOCONV;
 }
 
+// The same iteration without the bracket's upper end, which costs an atan2, a
+// square root and three divisions and is needed only when the iteration comes
+// near it.  True: converged, and newton_barrel within barrel_bracket takes the
+// same steps to the same s (*evals counts them).  False: the caller runs that.
+// Why the same: at every point tried here r grows along the path (dr/ds >= 0.2)
+// and less than 3 rad are turned, so the point lies on the rising arc between
+// the circle's closest and farthest points that the start's arc leads onto,
+// before the farthest one by a margin (at least 0.02 rad, or a good half turn
+// where the circle is large against r) that the bracket's rounding cannot
+// reach; the farthest point then clears r_l by 1e-3 circle radii, more than
+// the tolerance (the |h| tol bound), so that the radius is reachable; and the
+// bracket's ends that the points themselves set are kept here too.
+template <typename T>
+KF_HD inline bool newton_open(T x, T y, T phi, T h, T r_l, T s, int max_it, T tol, T* s_out, int* evals)
+{
+    const T ah = Tr<T>::abs_(h);
+    if (!(ah * tol * T(4000) <= T(1))) return false;
+    T s_lo = T(0), s_hi = T(1e30);
+    if (s < s_lo) s = s_lo;
+    for (int it = 1; it <= max_it; ++it) {
+        if (!(ah * s <= T(3)) || !(s < T(1e29))) return false;
+        HelixPoint<T> q = helix_at(x, y, phi, h, s);
+        T r = Tr<T>::sqrt_(q.X * q.X + q.Y * q.Y);
+        T res = r - r_l;
+        T drds = (q.X * q.cph + q.Y * q.sph) / r;
+        if (!(drds >= T(0.2))) return false;
+        if (res < T(0)) {
+            if (s > s_lo) s_lo = s;
+        } else {
+            if (s < s_hi) s_hi = s;
+        }
+        if (Tr<T>::abs_(res) < tol) {
+            *s_out = s - res / drds;
+            *evals += it;
+            return true;
+        }
+        const T sn = s - res / drds;
+        if (!(sn > s_lo && sn < s_hi)) return false;
+        s = sn;
+    }
+    return false;
+}
+
+// F P F^T of the transport to a barrel (KIND 0), a disk (KIND 1) or either
+// (KIND -1), the rows of F for x, y, z and phi given (F's other two are unit
+// rows).  A known kind leaves out the products with F's zeros and ones: 158
+// (barrel) and 146 (disk) of the 210 multiplications, in the same order, so
+// the sums are the same for finite P.
+template <int KIND>
+KF_HD constexpr bool transport_nz(int r, int k)
+{
+    // row r of F: 0 x, 1 y, 2 z, 3 phi
+    if (KIND == 0) return k == 0 || k == 1 || k == 3 || k == 4 || (r == 2 && (k == 2 || k == 5));
+    if (KIND == 1) {
+        if (r == 2) return k == 2 || k == 5;
+        return k == r || k >= 2;
+    }
+    return true;
+}
+
+// Keeps the compiler from interleaving what stands before and after: the rows
+// of the product below one after the other need 40 registers fewer than all at
+// once.
+KF_HD inline void sched_fence()
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_sched_barrier(0);
+#endif
+}
+
+template <int KIND, typename T, typename C>
+KF_HD inline void sandwich(const T F[4][6], C P[21])
+{
+    constexpr int gen[4] = {0, 1, 2, 4};       // the general rows of F
+    // P' = (F P) F^T (upper triangle), row by row of F P; F's unit rows 3 and 5
+    // take P's own rows and columns
+    C Pn[21];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = gen[r];
+        C A[6];
+#pragma unroll
+        for (int j = 0; j < 6; ++j) {
+            C acc = C(0);
+#pragma unroll
+            for (int k = 0; k < 6; ++k)
+                if (transport_nz<KIND>(r, k)) acc += C(F[r][k]) * P[pk(k, j)];
+            A[j] = acc;
+        }
+#pragma unroll
+        for (int q = r; q < 4; ++q) {
+            C acc = C(0);
+#pragma unroll
+            for (int k = 0; k < 6; ++k)
+                if (transport_nz<KIND>(q, k)) acc += A[k] * C(F[q][k]);
+            Pn[pk(i, gen[q])] = acc;
+        }
+        if (i < 3) Pn[pk(i, 3)] = A[3];
+        Pn[pk(i, 5)] = A[5];
+        sched_fence();
+    }
+    {
+        C acc = C(0);
+#pragma unroll
+        for (int k = 0; k < 6; ++k)
+            if (transport_nz<KIND>(3, k)) acc += P[pk(3, k)] * C(F[3][k]);
+        Pn[pk(3, 4)] = acc;
+    }
+    Pn[pk(3, 3)] = P[pk(3, 3)];
+    Pn[pk(3, 5)] = P[pk(3, 5)];
+    Pn[pk(5, 5)] = P[pk(5, 5)];
+#pragma unroll
+    for (int k = 0; k < 21; ++k) P[k] = Pn[k];
+    sched_fence();
+}
+
+// A covariance with an entry that is not finite becomes NaN throughout, as the
+// full product F P F^T makes it, so that leaving out zeros hides nothing.
+template <typename C>
+KF_HD inline void poison_nonfinite(C P[21])
+{
+    C z = C(0);
+#pragma unroll
+    for (int k = 0; k < 21; ++k) z += C(0) * P[k];
+    if (!(z == C(0))) {
+#pragma unroll
+        for (int k = 0; k < 21; ++k) P[k] = z;
+    }
+}
+
+// Whether every active lane of the wave is on a surface of this kind (host
+// code: whether this one is).
+KF_HD inline bool wave_all(bool c)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __ballot(!c) == 0;
+#else
+    return c;
+#endif
+}
+
 // Transport of (p, P) by arc length s to a surface: new state, F P F^T.
 // kind 0: barrel (path length from r(s) = r_l); 1: disk at z = zd.  The
 // helix and the Jacobian are evaluated in T; the state p is held in S (S may
 // be wider than T: the position and azimuth then advance by increments
 // computed in T and added in S, so the predicted state carries no rounding
 // to T before the update that consumes it); F P F^T is accumulated in C.
+// st, ct: sine and cosine of theta, which the transport leaves as it is.
 template <typename T, typename C, typename S>
-KF_HD inline void transport(S p[6], C P[21], T s, T kb, int kind, T zd)
+KF_HD inline void transport(S p[6], C P[21], T s, T kb, int kind, T zd, T st, T ct)
 {
-    const T x = T(p[0]), y = T(p[1]), z = T(p[2]), c = T(p[3]), phi = T(p[4]), th = T(p[5]);
+    const T x = T(p[0]), y = T(p[1]), z = T(p[2]), c = T(p[3]), phi = T(p[4]);
     const T h = -kb * c;
     HelixPoint<T> q = helix_at(x, y, phi, h, s);
-    T st, ct;
-    Tr<T>::sincos_(th, &st, &ct);
     const T cot = ct / st;
     const T u = T(0.5) * h * s;
     const T dsc = dsinc_of(u, q.su, q.cu);
@@ -221,65 +361,41 @@ KF_HD inline void transport(S p[6], C P[21], T s, T kb, int kind, T zd)
         d2 = -st / ct;
         d5 = (zd - z) / (ct * ct);
     }
-    const C F[4][6] = {
+    const T F[4][6] = {
         {T(1) + f0 * d0, f0 * d1, f0 * d2, D03 + f0 * d3, D04 + f0 * d4, f0 * d5},
         {f1 * d0, T(1) + f1 * d1, f1 * d2, D13 + f1 * d3, D14 + f1 * d4, f1 * d5},
         {f2 * d0, f2 * d1, T(1) + f2 * d2, f2 * d3, f2 * d4, D25 + f2 * d5},
         {f4 * d0, f4 * d1, f4 * d2, D43 + f4 * d3, T(1) + f4 * d4, f4 * d5},
     };
-    // A = F P for the four general rows; rows 3 and 5 of F are unit rows
-    C A[4][6];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int j = 0; j < 6; ++j) {
-            C acc = C(0);
-#pragma unroll
-            for (int k = 0; k < 6; ++k) acc += F[r][k] * P[pk(k, j)];
-            A[r][j] = acc;
-        }
-    // P' = A F^T (upper triangle).  Row of P' for F-row index: general rows use A,
-    // unit rows 3 and 5 use P itself.
-    C Pn[21];
-#pragma unroll
-    for (int i = 0; i < 6; ++i)
-#pragma unroll
-        for (int j = i; j < 6; ++j) {
-            // pick row i of (F P): general or unit
-            const int ri = i == 0 ? 0 : i == 1 ? 1 : i == 2 ? 2 : i == 4 ? 3 : -1;
-            const int rj = j == 0 ? 0 : j == 1 ? 1 : j == 2 ? 2 : j == 4 ? 3 : -1;
-            C v;
-            if (rj < 0) {
-                // column j of F^T is e_j: (F P)_{i j}
-                v = ri >= 0 ? A[ri][j] : P[pk(i, j)];
-            } else {
-                C acc = C(0);
-#pragma unroll
-                for (int k = 0; k < 6; ++k) acc += (ri >= 0 ? A[ri][k] : P[pk(i, k)]) * F[rj][k];
-                v = acc;
-            }
-            Pn[pk(i, j)] = v;
-        }
-#pragma unroll
-    for (int k = 0; k < 21; ++k) P[k] = Pn[k];
+    // the sparse product where the whole wave is on one kind of surface
+    if (wave_all(kind == 0))
+        sandwich<0>(F, P);
+    else
+        sandwich<-1>(F, P);
     p[0] = p[0] + S(s * q.ca * q.sc);
     p[1] = p[1] + S(s * q.sa * q.sc);
     p[2] = p[2] + S(s * cot);
     p[4] = wrap_phi(p[4] + S(h * s));
 }
 
+template <typename T, typename C, typename S>
+KF_HD inline void transport(S p[6], C P[21], T s, T kb, int kind, T zd)
+{
+    T st, ct;
+    Tr<T>::sincos_(T(p[5]), &st, &ct);
+    transport(p, P, s, kb, kind, zd, st, ct);
+}
+
 // Multiple-scattering process noise of a layer (PDG Highland width), added to
 // the (c, phi, theta) block at the propagated state.  Evaluated in T on the
-// state (held in S) rounded to T.
+// state (held in S) rounded to T.  st, ct: sine and cosine of theta.
 template <typename T, typename C, typename S>
-KF_HD inline void add_scatter(const S ps[6], C P[21], int kind, T x0, T mass)
+KF_HD inline void add_scatter(const S ps[6], C P[21], int kind, T x0, T mass, T st, T ct)
 {
     if (!(x0 > T(0))) return;
     T p[6];
 #pragma unroll
     for (int k = 0; k < 6; ++k) p[k] = T(ps[k]);
-    T st, ct;
-    Tr<T>::sincos_(p[5], &st, &ct);
     T cosa;
     if (kind == 0) {
         T sph, cph;
@@ -302,6 +418,15 @@ KF_HD inline void add_scatter(const S ps[6], C P[21], int kind, T x0, T mass)
     P[pk(5, 5)] += C(t2);
     P[pk(3, 5)] += C(-p[3] * cot * t2);
     P[pk(3, 3)] += C(p[3] * p[3] * cot * cot * t2);
+}
+
+template <typename T, typename C, typename S>
+KF_HD inline void add_scatter(const S ps[6], C P[21], int kind, T x0, T mass)
+{
+    if (!(x0 > T(0))) return;
+    T st, ct;
+    Tr<T>::sincos_(T(ps[5]), &st, &ct);
+    add_scatter(ps, P, kind, x0, mass, st, ct);
 }
 
 // Mean ionisation loss in silicon [MeV cm^2/g]: the Bethe formula with the
@@ -328,11 +453,13 @@ KF_HD inline T bethe_si(T p, T m)
 // covariance's c row and column scaled by dc'/dc = (p/p')^3 E'/E).
 // The state is held in S; the lookup takes the crossing point in double, the
 // noise and the loss are evaluated in T, and q/pT is scaled in S.
-template <typename T, typename C, typename S>
-KF_HD inline void add_material(S ps[6], C P[21], const kf_layer& L, const MatMap& m, T mass)
+template <typename T, typename C, typename S, typename LT>
+KF_HD inline void add_material(S ps[6], C P[21], const LT& L, const MatMap& m, T mass)
 {
+    T st, ct;
+    Tr<T>::sincos_(T(ps[5]), &st, &ct);
     if (!m.x0) {
-        add_scatter(ps, P, L.kind, T(L.x0), mass);
+        add_scatter(ps, P, L.kind, T(L.x0), mass, st, ct);
         return;
     }
     const double r = sqrt((double)ps[0] * (double)ps[0] + (double)ps[1] * (double)ps[1]);
@@ -341,13 +468,11 @@ KF_HD inline void add_material(S ps[6], C P[21], const kf_layer& L, const MatMap
     ir = ir < 0 ? 0 : (ir >= m.nr ? m.nr - 1 : ir);
     iz = iz < 0 ? 0 : (iz >= m.nz ? m.nz - 1 : iz);
     const T x0 = T(m.x0[ir * m.nz + iz]), xi = T(m.xi[ir * m.nz + iz]);
-    add_scatter(ps, P, L.kind, x0, mass);
+    add_scatter(ps, P, L.kind, x0, mass, st, ct);
     if (!(xi > T(0))) return;
     T p[6];
 #pragma unroll
     for (int k = 0; k < 6; ++k) p[k] = T(ps[k]);
-    T st, ct;
-    Tr<T>::sincos_(p[5], &st, &ct);
     T cosa;
     if (L.kind == 0) {
         T sph, cph;
@@ -391,8 +516,15 @@ KF_HD inline HitFrame<U> hit_frame(float x, float y, float z, float su, float sv
     f.hy = U(y);
     f.hz = U(z);
     U rho = Tr<U>::sqrt_(f.hx * f.hx + f.hy * f.hy);
-    f.c = f.hx / rho;
-    f.s = f.hy / rho;
+    if constexpr (sizeof(U) == 8) {
+        // in 64 bits one division serves both (an ulp off a division each)
+        const U inv = U(1) / rho;
+        f.c = f.hx * inv;
+        f.s = f.hy * inv;
+    } else {
+        f.c = f.hx / rho;
+        f.s = f.hy / rho;
+    }
     f.vu = U(su) * U(su);
     f.vv = U(sv) * U(sv);
     return f;
@@ -435,25 +567,28 @@ KF_HD inline U hit_chi2(const T p[6], const C P[21], const HitFrame<U>& f, int k
 // Kalman update with a 2D hit.  Gain K = P H^T S^-1, state x + K r, covariance
 // in Joseph form (I - K H) P (I - K H)^T + K V K^T, evaluated as
 // M = P - K (H P), P+ = M - (M H^T) K^T + K V K^T.  Returns status bits.
-template <typename T, typename C, typename U>
-KF_HD inline int kf_update(T p[6], C P[21], const HitFrame<U>& f, int kind, U* chi2_out)
+// KIND 0 or 1 (known) or -1 (kind decides): for a barrel the second row of H
+// is the unit vector of z, and no products are taken with it.
+template <int KIND, typename T, typename C, typename U>
+KF_HD inline int kf_update_kind(T p[6], C P[21], const HitFrame<U>& f, int kind, U* chi2_out)
 {
+    const bool barrel = KIND == 0 || (KIND < 0 && kind == 0);
     const U c = f.c, s = f.s;
     U Pu[21];
 #pragma unroll
     for (int k = 0; k < 21; ++k) Pu[k] = U(P[k]);
     U ru = -s * (f.hx - U(p[0])) + c * (f.hy - U(p[1]));
-    U rv = kind == 0 ? f.hz - U(p[2]) : c * (f.hx - U(p[0])) + s * (f.hy - U(p[1]));
+    U rv = barrel ? f.hz - U(p[2]) : c * (f.hx - U(p[0])) + s * (f.hy - U(p[1]));
     // B = P H^T (6x2)
     U B0[6], B1[6];
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
         B0[i] = -s * Pu[pk(i, 0)] + c * Pu[pk(i, 1)];
-        B1[i] = kind == 0 ? Pu[pk(i, 2)] : c * Pu[pk(i, 0)] + s * Pu[pk(i, 1)];
+        B1[i] = barrel ? Pu[pk(i, 2)] : c * Pu[pk(i, 0)] + s * Pu[pk(i, 1)];
     }
     U S00 = -s * B0[0] + c * B0[1] + f.vu;
     U S01 = -s * B1[0] + c * B1[1];
-    U S11 = (kind == 0 ? B1[2] : c * B1[0] + s * B1[1]) + f.vv;
+    U S11 = (barrel ? B1[2] : c * B1[0] + s * B1[1]) + f.vv;
     U det = S00 * S11 - S01 * S01;
     if (!(det > U(0)) || !(S00 > U(0))) return KF_ST_NONPD;
     U idet = U(1) / det;
@@ -479,20 +614,35 @@ KF_HD inline int kf_update(T p[6], C P[21], const HitFrame<U>& f, int kind, U* c
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
         N0[i] = -s * Mc[i][0] + c * Mc[i][1];
-        N1[i] = kind == 0 ? Mc[i][2] : c * Mc[i][0] + s * Mc[i][1];
+        N1[i] = barrel ? Mc[i][2] : c * Mc[i][0] + s * Mc[i][1];
     }
 #pragma unroll
-    for (int i = 0; i < 6; ++i)
+    for (int i = 0; i < 6; ++i) {
+        // in 64 bits the two terms along each gain column are taken together
+        // (K V - N first: 12 products instead of 42)
+        const U L0 = f.vu * K0[i] - N0[i], L1 = f.vv * K1[i] - N1[i];
 #pragma unroll
         for (int j = i; j < 6; ++j) {
             U m = j < 3 ? Mc[i][j] : Pu[pk(i, j)] - K0[i] * B0[j] - K1[i] * B1[j];
-            U v = m - N0[i] * K0[j] - N1[i] * K1[j] + f.vu * K0[i] * K0[j] + f.vv * K1[i] * K1[j];
+            U v;
+            if constexpr (sizeof(U) == 8)
+                v = m + L0 * K0[j] + L1 * K1[j];
+            else
+                v = m - N0[i] * K0[j] - N1[i] * K1[j] + f.vu * K0[i] * K0[j] + f.vv * K1[i] * K1[j];
             P[pk(i, j)] = C(v);
         }
+    }
     bool fin = true;
 #pragma unroll
     for (int i = 0; i < 6; ++i) fin &= isfinite(p[i]);
     return fin ? 0 : KF_ST_NAN;
+}
+
+template <typename T, typename C, typename U>
+KF_HD inline int kf_update(T p[6], C P[21], const HitFrame<U>& f, int kind, U* chi2_out)
+{
+    if (wave_all(kind == 0)) return kf_update_kind<0, T, C, U>(p, P, f, kind, chi2_out);
+    return kf_update_kind<-1, T, C, U>(p, P, f, kind, chi2_out);
 }
 
 // ---------------------------------------------------------------- parametrised field
@@ -661,49 +811,109 @@ KF_HD inline void field_transport(S p[6], C P[21], const T q[6], T l, const kf_p
 // fallback bit of the learned guess).
 constexpr uint32_t kFreezeMask = ~(uint32_t)KF_ST_FALLBACK;
 
-// Surface orders for the dynamic navigation, built once per workgroup:
-// barrel indices by radius (ascending, ties by index) and disk indices in
-// layer order.
-struct NavOrder {
-    int8_t barrel[64];
-    int8_t disk[64];
-    int32_t nb, nd;
+// One layer as the finding kernel reads it: the caller's record with its
+// lengths in T = float (to which the kernel would round them at each use) and
+// its bins, in three 16-byte reads.
+struct alignas(16) FindLayer {
+    float r_or_z, lo, hi, x0;
+    float win_su, win_sv;
+    int32_t kind, nbin_phi;
+    int32_t nbin_2, base;      // second bins; the layer's first bin in its event
+    int32_t pad[2];
 };
 
-KF_HD inline void build_nav_order(const kf_layer* L, int nl, NavOrder* nv)
+// Surface orders for the dynamic navigation, built once per workgroup:
+// barrel radii and their layers by radius (ascending, ties by index), disk
+// planes, radial extents and layers in layer order, each padded to a multiple
+// of four with values that no test passes.
+struct NavOrder {
+    const float *br, *dz, *dlo, *dhi;
+    const int8_t *barrel, *disk;
+    int nb, nd;
+};
+
+// bytes behind the views of a NavOrder of nl layers
+KF_HD inline int nav_bytes(int nl)
 {
-    nv->nb = nv->nd = 0;
-    for (int l = 0; l < nl; ++l) {
-        if (L[l].kind == 0) {
-            // stable insertion by radius
-            int k = nv->nb++;
-            while (k > 0 && L[nv->barrel[k - 1]].r_or_z > L[l].r_or_z) {
-                nv->barrel[k] = nv->barrel[k - 1];
-                --k;
-            }
-            nv->barrel[k] = (int8_t)l;
-        } else {
-            nv->disk[nv->nd++] = (int8_t)l;
-        }
-    }
+    const int n4 = (nl + 3) & ~3;
+    return 4 * n4 * (int)sizeof(float) + 2 * n4;
 }
 
-// The next barrel outward from the radius-ordered list: the first above
-// rho + kNextBarrelEps (the same layer as next_barrel below), or -1.
-template <typename T>
-KF_HD inline int next_barrel(const T p[6], const kf_layer* L, const NavOrder& nv)
+KF_HD inline NavOrder nav_view(void* mem, int nl, int nb)
 {
-    const T rho = Tr<T>::sqrt_(p[0] * p[0] + p[1] * p[1]);
-    for (int k = 0; k < nv.nb; ++k) {
-        const int l = nv.barrel[k];
-        if (T(L[l].r_or_z) > rho + T(kNextBarrelEps)) return l;
+    const int n4 = (nl + 3) & ~3;
+    float* f = (float*)mem;
+    NavOrder v;
+    v.br = f;
+    v.dz = f + n4;
+    v.dlo = f + 2 * n4;
+    v.dhi = f + 3 * n4;
+    v.barrel = (const int8_t*)(f + 4 * n4);
+    v.disk = v.barrel + n4;
+    v.nb = nb;
+    v.nd = nl - nb;
+    return v;
+}
+
+// Layer l's place in the surface orders (every layer's by a lane of its own;
+// a lane beyond the layers pads).
+template <typename LT>
+KF_HD inline void nav_place(const LT* L, int nl, int l, void* mem)
+{
+    const int n4 = (nl + 3) & ~3;
+    float* f = (float*)mem;
+    int8_t* id = (int8_t*)(f + 4 * n4);
+    int nb = 0, before = 0;
+    for (int k = 0; k < nl; ++k) {
+        const bool barrel = L[k].kind == 0;
+        nb += barrel ? 1 : 0;
+        if (l >= nl) continue;
+        if (L[l].kind == 0)
+            before += barrel && (L[k].r_or_z < L[l].r_or_z || (L[k].r_or_z == L[l].r_or_z && k < l)) ? 1 : 0;
+        else
+            before += !barrel && k < l ? 1 : 0;
     }
-    return -1;
+    if (l < nl) {
+        if (L[l].kind == 0) {
+            f[before] = float(L[l].r_or_z);
+            id[before] = (int8_t)l;
+        } else {
+            f[n4 + before] = float(L[l].r_or_z);
+            f[2 * n4 + before] = float(L[l].lo);
+            f[3 * n4 + before] = float(L[l].hi);
+            id[n4 + before] = (int8_t)l;
+        }
+    }
+    // pads: no radius is beyond infinity, and no plane is ahead at NaN
+    if (l < n4 && l >= nb) f[l] = INFINITY;
+    if (l < n4 && l >= nl - nb) f[n4 + l] = NAN;
+}
+
+// The next barrel outward from the radius-ordered list: the place of the
+// first above rho + kNextBarrelEps (the same layer as next_barrel below), or
+// nb.  Radii rise, so it is the number of those not above.
+template <typename T>
+KF_HD inline int next_barrel_place(const T p[6], const NavOrder& nv)
+{
+    const T r = Tr<T>::sqrt_(p[0] * p[0] + p[1] * p[1]) + T(kNextBarrelEps);
+    int k = 0;
+    for (int i = 0; i < nv.nb; i += 4) {
+        const float4 b = *(const float4*)(nv.br + i);
+        k += (T(b.x) > r ? 0 : 1) + (T(b.y) > r ? 0 : 1) + (T(b.z) > r ? 0 : 1) + (T(b.w) > r ? 0 : 1);
+    }
+    return k < nv.nb ? k : nv.nb;
+}
+
+template <typename T>
+KF_HD inline int next_barrel(const T p[6], const NavOrder& nv)
+{
+    const int k = next_barrel_place(p, nv);
+    return k < nv.nb ? nv.barrel[k] : -1;
 }
 
 // The next barrel outward: smallest radius above rho + kNextBarrelEps, or -1.
-template <typename T>
-KF_HD inline int next_barrel(const T p[6], const kf_layer* L, int nl)
+template <typename T, typename LT>
+KF_HD inline int next_barrel(const T p[6], const LT* L, int nl)
 {
     const T rho = Tr<T>::sqrt_(p[0] * p[0] + p[1] * p[1]);
     int bl = -1;
@@ -742,6 +952,44 @@ KF_HD inline int solve_barrel(const T p[6], T h, T cph, T sph, T r_l, T s_hi, co
     }
     return newton_barrel(p[0], p[1], p[4], h, r_l, s0, T(0), s_hi, prm.max_newton,
                          T(prm.newton_tol), s, evals);
+}
+
+// Propagate to a barrel of radius r_l: 0 with the path length *s,
+// KF_ST_UNREACHABLE or KF_ST_NOCONV.  The open iteration first; where it gives
+// up, the bracket and the bracketed solve.
+template <typename T>
+KF_HD inline int reach_barrel(const T p[6], T h, T cph, T sph, T r_l, const kf_params& prm, T s_guess,
+                              int learned_it, T* s, int* evals, int* fallbacks)
+{
+    const T tol = T(prm.newton_tol);
+    T s0 = line_guess(p[0], p[1], cph, sph, r_l);
+    int it = prm.max_newton;
+    if (s_guess >= T(0) && learned_it > 0 && Tr<T>::abs_(s_guess - s0) > T(kLearnedGate * prm.newton_tol)) {
+        s0 = s_guess;
+        it = learned_it;
+    }
+    if (newton_open(p[0], p[1], p[4], h, r_l, s0, it, tol, s, evals)) return 0;
+    T s_hi;
+    if (!barrel_bracket(p[0], p[1], cph, sph, h, r_l, &s_hi)) return KF_ST_UNREACHABLE;
+    return solve_barrel(p, h, cph, sph, r_l, s_hi, prm, s_guess, learned_it, s, evals, fallbacks);
+}
+
+// s within half a turn of curvature hh = |h| (s <= pi / hh): the division only
+// near the limit.
+template <typename T>
+KF_HD inline bool within_half_turn(T s, T hh)
+{
+    if (s * hh < T(3.14)) return true;
+    const T s_max = hh > T(0) ? T(kPi) / hh : T(1e30);
+    return s <= s_max;
+}
+
+template <typename T>
+KF_HD inline bool beyond_half_turn(T s, T hh)
+{
+    if (s * hh < T(3.14)) return false;
+    const T s_max = hh > T(0) ? T(kPi) / hh : T(1e30);
+    return s > s_max;
 }
 
 // Propagate-to-radius in the parametrised field: bracketed Newton on the 3D
@@ -869,8 +1117,8 @@ KF_HD inline int solve_disk_field(const T p[6], T z_d, const kf_params& prm, T* 
 // -1 (no surface left; a failed solve sets NOCONV).  l_guess >= 0: the
 // learned start of the barrel solve (3D path), with learned_it evaluations
 // before the fallback (counted in *fallbacks).
-template <typename T>
-KF_HD inline int navigate_field(const T p[6], const kf_layer* L, int nl, const kf_params& prm,
+template <typename T, typename LT>
+KF_HD inline int navigate_field(const T p[6], const LT* L, int nl, const kf_params& prm,
                                 T* l_out, T q[6], uint32_t* st, int* newton_evals, int* disk_evals,
                                 T l_guess = T(-1), int learned_it = 0, int* fallbacks = nullptr)
 {
@@ -936,8 +1184,8 @@ KF_HD inline int navigate_field(const T p[6], const kf_layer* L, int nl, const k
 // transverse path exceeds half a turn by more than 1% + 1 cm is not solved.
 // Returns the layer with the 3D path and the end state, or -1 when the plan
 // is exhausted (a failed solve sets NOCONV and returns -1).
-template <typename T>
-KF_HD inline int steer_next_field(const T p[6], const kf_layer* L, const uint8_t* plan, int n_plan,
+template <typename T, typename LT>
+KF_HD inline int steer_next_field(const T p[6], const LT* L, const uint8_t* plan, int n_plan,
                                   int* pos, const kf_params& prm, T* l_out, T q[6], uint32_t* st,
                                   int* newton_evals, int* disk_evals)
 {
@@ -952,7 +1200,7 @@ KF_HD inline int steer_next_field(const T p[6], const kf_layer* L, const uint8_t
     Tr<T>::sincos_(p[5], &sth, &cth);
     for (int qi = *pos; qi < n_plan; ++qi) {
         const int l = plan[qi];
-        const kf_layer& Ly = L[l];
+        const LT& Ly = L[l];
         T ll;
         if (Ly.kind == 0) {
             const T r_l = T(Ly.r_or_z);
@@ -995,41 +1243,39 @@ KF_HD inline int steer_next_field(const T p[6], const kf_layer* L, const uint8_t
 // radial extent); entries not reached are passed over.  Returns the layer,
 // its path length and *pos past it, or -1 when the plan is exhausted (a
 // failed barrel solve sets NOCONV and returns -1).
-template <typename T>
-KF_HD inline int steer_next(const T p[6], const kf_layer* L, const uint8_t* plan, int n_plan,
-                            int* pos, const kf_params& prm, T kb, T* s_out, uint32_t* st,
+template <typename T, typename LT>
+KF_HD inline int steer_next(const T p[6], const LT* L, const uint8_t* plan, int n_plan,
+                            int* pos, const kf_params& prm, T kb, T sth, T cth, T* s_out, uint32_t* st,
                             int* newton_evals, int* disk_evals)
 {
     const T hh = Tr<T>::abs_(kb * p[3]);
-    const T s_max = hh > T(0) ? T(kPi) / hh : T(1e30);
     const T rho = Tr<T>::sqrt_(p[0] * p[0] + p[1] * p[1]);
-    T sth, cth, sph, cph;
-    Tr<T>::sincos_(p[5], &sth, &cth);
+    T sph, cph;
     Tr<T>::sincos_(p[4], &sph, &cph);
     const T cot = cth / sth;
     const T h = -kb * p[3];
     for (int q = *pos; q < n_plan; ++q) {
         const int l = plan[q];
-        const kf_layer& Ly = L[l];
+        const LT& Ly = L[l];
         T s;
         if (Ly.kind == 0) {
             const T r_l = T(Ly.r_or_z);
             if (!(r_l > rho + T(kNextBarrelEps))) continue;
-            T s_hi;
-            if (!barrel_bracket(p[0], p[1], cph, sph, h, r_l, &s_hi)) continue;
             int fb = 0;
-            if (solve_barrel(p, h, cph, sph, r_l, s_hi, prm, T(-1), 0, &s, newton_evals, &fb)) {
+            const int r = reach_barrel(p, h, cph, sph, r_l, prm, T(-1), 0, &s, newton_evals, &fb);
+            if (r == (int)KF_ST_UNREACHABLE) continue;
+            if (r) {
                 *st |= KF_ST_NOCONV;
                 *pos = q + 1;
                 return -1;
             }
             const T zc = p[2] + s * cot;
-            if (Tr<T>::abs_(zc) > T(Ly.hi) || s > s_max) continue;
+            if (Tr<T>::abs_(zc) > T(Ly.hi) || beyond_half_turn(s, hh)) continue;
         } else {
             const T dz = T(Ly.r_or_z) - p[2];
             if (!(dz * cot > T(0)) || Tr<T>::abs_(dz) <= T(kDiskAheadEps)) continue;
             s = dz / cot;
-            if (s > s_max) continue;
+            if (beyond_half_turn(s, hh)) continue;
             ++*disk_evals;
             const HelixPoint<T> hp = helix_at(p[0], p[1], p[4], h, s);
             const T r = Tr<T>::sqrt_(hp.X * hp.X + hp.Y * hp.Y);
@@ -1048,55 +1294,59 @@ KF_HD inline int steer_next(const T p[6], const kf_layer* L, const uint8_t* plan
 // its z extent) or the first disk ahead whose crossing is inside its radial
 // extent.  Returns the layer (or -1) and the path length.  s_guess >= 0: the
 // learned start of the barrel solve (learned_it evaluations, then fallback).
-template <typename T>
-KF_HD inline int navigate(const T p[6], const kf_layer* L, const NavOrder& nv, const kf_params& prm, T kb,
-                          T* s_out, uint32_t* st, int* newton_evals, int* disk_evals,
+// sth, cth: sine and cosine of theta.
+template <typename T, typename LT>
+KF_HD inline int navigate(const T p[6], const LT* L, const NavOrder& nv, const kf_params& prm, T kb,
+                          T sth, T cth, T* s_out, uint32_t* st, int* newton_evals, int* disk_evals,
                           T s_guess = T(-1), int learned_it = 0, int* fallbacks = nullptr)
 {
     // only surfaces reached within half a turn in the transverse plane
     const T hh = Tr<T>::abs_(kb * p[3]);
-    const T s_max = hh > T(0) ? T(kPi) / hh : T(1e30);
-    const int bl = next_barrel(p, L, nv);
-    const T rbl = bl >= 0 ? T(L[bl].r_or_z) : T(0);
+    const T h = -kb * p[3];
+    const int bk = next_barrel_place(p, nv);
     T best_s = T(1e30);
     int best_l = -1;
-    T sth, cth;
-    Tr<T>::sincos_(p[5], &sth, &cth);
-    if (bl >= 0) {
-        const T h = -kb * p[3];
+    if (bk < nv.nb) {
+        const int bl = nv.barrel[bk];
         T sph, cph;
         Tr<T>::sincos_(p[4], &sph, &cph);
-        T s_hi;
-        if (barrel_bracket(p[0], p[1], cph, sph, h, rbl, &s_hi)) {
-            T s;
-            int fb = 0;
-            const int r = solve_barrel(p, h, cph, sph, rbl, s_hi, prm, s_guess, learned_it, &s,
-                                       newton_evals, &fb);
+        T s;
+        int fb = 0;
+        const int r = reach_barrel(p, h, cph, sph, T(nv.br[bk]), prm, s_guess, learned_it, &s,
+                                   newton_evals, &fb);
+        if (r != (int)KF_ST_UNREACHABLE) {
             if (fallbacks) *fallbacks += fb;
             if (r) {
                 *st |= KF_ST_NOCONV;
                 return -1;
             }
             const T zc = p[2] + s * cth / sth;
-            if (Tr<T>::abs_(zc) <= T(L[bl].hi) && s <= s_max) {
+            if (Tr<T>::abs_(zc) <= T(L[bl].hi) && within_half_turn(s, hh)) {
                 best_s = s;
                 best_l = bl;
             }
         }
     }
     const T cot = cth / sth;
-    for (int k = 0; k < nv.nd; ++k) {
-        const int l = nv.disk[k];
-        const T dz = T(L[l].r_or_z) - p[2];
-        if (!(dz * cot > T(0)) || Tr<T>::abs_(dz) <= T(kDiskAheadEps)) continue;
-        const T s = dz / cot;
-        if (!(s < best_s) || s > s_max) continue;
-        ++*disk_evals;
-        const HelixPoint<T> q = helix_at(p[0], p[1], p[4], -kb * p[3], s);
-        const T r = Tr<T>::sqrt_(q.X * q.X + q.Y * q.Y);
-        if (r < T(L[l].lo) || r > T(L[l].hi)) continue;
-        best_s = s;
-        best_l = l;
+    const T acot = T(1.00001) * Tr<T>::abs_(cot);
+    for (int k0 = 0; k0 < nv.nd; k0 += 4) {
+        const float4 z4 = *(const float4*)(nv.dz + k0);
+        const float zz[4] = {z4.x, z4.y, z4.z, z4.w};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const T dz = T(zz[u]) - p[2];
+            if (!(dz * cot > T(0)) || Tr<T>::abs_(dz) <= T(kDiskAheadEps)) continue;
+            // further than the best surface for certain: no division
+            if (Tr<T>::abs_(dz) > best_s * acot) continue;
+            const T s = dz / cot;
+            if (!(s < best_s) || beyond_half_turn(s, hh)) continue;
+            ++*disk_evals;
+            const HelixPoint<T> q = helix_at(p[0], p[1], p[4], h, s);
+            const T r = Tr<T>::sqrt_(q.X * q.X + q.Y * q.Y);
+            if (r < T(nv.dlo[k0 + u]) || r > T(nv.dhi[k0 + u])) continue;
+            best_s = s;
+            best_l = nv.disk[k0 + u];
+        }
     }
     *s_out = best_s;
     return best_l;
@@ -1115,8 +1365,8 @@ struct Window {
     T dphi, cos_dphi, sin_dphi, wv, vlo, vhi;
 };
 
-template <typename T, typename C>
-KF_HD inline Window<T> make_window(const T p[6], const C P[21], const kf_layer& L, T cut)
+template <typename T, typename C, typename LT>
+KF_HD inline Window<T> make_window(const T p[6], const C P[21], const LT& L, T cut)
 {
     Window<T> W;
     const T rho = Tr<T>::sqrt_(p[0] * p[0] + p[1] * p[1]);
@@ -1127,8 +1377,10 @@ KF_HD inline Window<T> make_window(const T p[6], const C P[21], const kf_layer& 
     if (dphi > T(0.5 * kPi)) dphi = T(kPi);
     W.dphi = dphi;
     W.all_phi = dphi >= T(kPi);
-    W.cos_dphi = W.all_phi ? T(-1) : Tr<T>::cos_(dphi);
-    W.sin_dphi = W.all_phi ? T(2) : Tr<T>::sin_(dphi);
+    T sd, cd;
+    Tr<T>::sincos_(dphi, &sd, &cd);
+    W.cos_dphi = W.all_phi ? T(-1) : cd;
+    W.sin_dphi = W.all_phi ? T(2) : sd;
     if (L.kind == 0) {
         W.wv = T(1.001) * Tr<T>::sqrt_(cut * (pzz + T(L.win_sv) * T(L.win_sv))) + T(1e-4);
         W.vlo = p[2] - W.wv;

@@ -186,8 +186,8 @@ __device__ inline float mlp_target(const float f[kMlpIn], float path)
 // curvature in the field at the start point, target radius or disk z over
 // 100, straight-line path length over 100 (tangent-line intersection / exact
 // disk path), cot theta, z/100.
-template <typename T>
-__device__ inline void mlp_features(const T p[6], const kf_layer& L, const kf_params& prm,
+template <typename T, typename LT>
+__device__ inline void mlp_features(const T p[6], const LT& L, const kf_params& prm,
                                     float f[kMlpIn])
 {
     T bz = T(prm.bz);

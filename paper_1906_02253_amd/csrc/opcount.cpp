@@ -146,7 +146,7 @@ int main()
         add_scatter(q, Q, 1, T(0.02), T(prm.mass));
     });
     // hit-search window and the per-hit tests (azimuth, second coordinate, chi2)
-    Tally window = count([&] { make_window<T, T>(p, P, barrel, T(30.0)); });
+    Tally window = count([&] { make_window<T, T, kf_layer>(p, P, barrel, T(30.0)); });
     HitFrame<T> f;
     f.hx = 28.7;
     f.hy = 8.9;
