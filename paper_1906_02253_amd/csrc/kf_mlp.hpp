@@ -27,24 +27,34 @@ constexpr int kMlpOffB1 = 512, kMlpOffW2 = 576, kMlpOffB2 = 4672, kMlpOffW3 = 47
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// float -> bf16, round to nearest even (NaN stays NaN)
-__device__ inline uint16_t to_bf16(float f)
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// two floats -> bf16, round to nearest even (NaN stays NaN), low half first:
+// one v_cvt_pk_bf16_f32
+__device__ inline uint32_t to_bf16x2(float a, float b)
 {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7f800000u) == 0x7f800000u) return (uint16_t)((u >> 16) | ((u & 0xffffu) ? 0x40u : 0u));
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
+    const f32x2 v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
+
+__device__ inline uint16_t to_bf16(float f) { return (uint16_t)to_bf16x2(f, f); }
 
 __device__ inline float from_bf16(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
-__device__ inline float round_bf16(float f) { return from_bf16(to_bf16(f)); }
-
-// tanh from the exponential: 1 - 2 / (e^{2x} + 1), saturated beyond |x| = 15
+// tanh from the exponential: 1 - 2 / (e^{2x} + 1), saturated beyond |x| = 15.
+// The quotient is the correctly rounded one: the division's own refinement of
+// the reciprocal without its scaling, which a denominator of 1 .. 1e13 does
+// not need (2 / d is twice 1 / d to the bit).
 __device__ inline float mlp_tanh(float x)
 {
-    x = fminf(fmaxf(x, -15.0f), 15.0f);
-    return 1.0f - __fdividef(2.0f, __expf(2.0f * x) + 1.0f);
+    x = __builtin_amdgcn_fmed3f(x, -15.0f, 15.0f);
+    const float d = __builtin_amdgcn_exp2f(x * 2.88539008f) + 1.0f;    // 2 log2(e)
+    float r = __builtin_amdgcn_rcpf(d);
+    r = __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r);
+    float q = __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r);
+    q = __builtin_fmaf(__builtin_fmaf(-d, q, 1.0f), r, q);
+    return __builtin_fmaf(-2.0f, q, 1.0f);
 }
 
 __device__ inline f32x4 mfma_bf16(bf16x4 a, bf16x4 b, f32x4 c)
@@ -66,17 +76,21 @@ __device__ inline bf16x4 load_bf16x4(const uint16_t* p)
 
 __device__ inline bf16x4 pack_bf16x4(float a, float b, float c, float d)
 {
-    bf16x4 r;
-    r[0] = (short)to_bf16(a);
-    r[1] = (short)to_bf16(b);
-    r[2] = (short)to_bf16(c);
-    r[3] = (short)to_bf16(d);
-    return r;
+    const uint2 v = make_uint2(to_bf16x2(a, b), to_bf16x2(c, d));
+    return __builtin_bit_cast(bf16x4, v);
 }
 
-// The part of x below its bf16 rounding, itself rounded to bf16: x_hi + x_lo
-// carries about 16 significant bits.
-__device__ inline float bf16_rest(float x) { return x - round_bf16(x); }
+// Four floats as high and low bf16 parts: the low part is what the rounding
+// to the high one left, itself rounded to bf16, so that their sum carries
+// about 16 significant bits.
+__device__ inline void split_bf16x4(const f32x4& x, bf16x4* hi, bf16x4* lo)
+{
+    const uint2 h = make_uint2(to_bf16x2(x[0], x[1]), to_bf16x2(x[2], x[3]));
+    const float l0 = x[0] - __uint_as_float(h.x << 16), l1 = x[1] - __uint_as_float(h.x & 0xffff0000u);
+    const float l2 = x[2] - __uint_as_float(h.y << 16), l3 = x[3] - __uint_as_float(h.y & 0xffff0000u);
+    *hi = __builtin_bit_cast(bf16x4, h);
+    *lo = pack_bf16x4(l0, l1, l2, l3);
+}
 
 // B operand of the transposed inputs of one 16-row tile from four lane
 // values v[0..3]: lane groups 0 and 1 hold the high bf16 parts of inputs
@@ -84,8 +98,9 @@ __device__ inline float bf16_rest(float x) { return x - round_bf16(x); }
 // layer's weights are stored twice along K, so one product sums both).
 __device__ inline bf16x4 split_inputs(const float v[4], int g)
 {
-    if (g < 2) return pack_bf16x4(v[0], v[1], v[2], v[3]);
-    return pack_bf16x4(bf16_rest(v[0]), bf16_rest(v[1]), bf16_rest(v[2]), bf16_rest(v[3]));
+    bf16x4 hi, lo;
+    split_bf16x4(f32x4{v[0], v[1], v[2], v[3]}, &hi, &lo);
+    return g < 2 ? hi : lo;
 }
 
 // Forward pass of one tile of 16 rows.  xb: split_inputs of the row l%16 of
@@ -103,12 +118,13 @@ __device__ inline float mlp_tile(const MlpDev& m, bf16x4 xb, f32x4 h1[4], f32x4 
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) {
         f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-        acc = mfma_bf16(load_bf16x4(m.w1 + (16 * mt + r) * 16 + 4 * g), xb, acc);
+        h1[mt] = mfma_bf16(load_bf16x4(m.w1 + (16 * mt + r) * 16 + 4 * g), xb, acc);
+    }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) h1[mt][j] = mlp_tanh(acc[j] + m.bias[16 * mt + 4 * g + j]);
-        hb[mt] = pack_bf16x4(h1[mt][0], h1[mt][1], h1[mt][2], h1[mt][3]);
-        hl[mt] = pack_bf16x4(bf16_rest(h1[mt][0]), bf16_rest(h1[mt][1]), bf16_rest(h1[mt][2]),
-                             bf16_rest(h1[mt][3]));
+    for (int mt = 0; mt < 4; ++mt) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) h1[mt][j] = mlp_tanh(h1[mt][j] + m.bias[16 * mt + 4 * g + j]);
+        split_bf16x4(h1[mt], &hb[mt], &hl[mt]);
     }
     float y = 0.0f;
 #pragma unroll
@@ -135,18 +151,24 @@ __device__ inline float mlp_tile(const MlpDev& m, bf16x4 xb, f32x4 h1[4], f32x4 
 
 // Whole-wave inference: lane L passes the inputs of its own row and gets its
 // own output.  Must be called by all 64 lanes (uniform control flow).  want:
-// the lanes whose output is used (a wave-uniform mask); the 16-row tile of a
-// group of 16 lanes none of which wants its output is skipped, and those
-// lanes get 0.
+// the lanes whose output is used (a wave-uniform mask); only their rows are
+// computed, packed into as few 16-row tiles as hold them, and the other lanes
+// get 0.  A row's output does not depend on its place in a tile.
 __device__ inline float mlp_wave(const MlpDev& m, const float f[kMlpIn], uint64_t want = ~0ull)
 {
     const int ln = (int)(threadIdx.x & 63);
     const int r = ln & 15, g = ln >> 4;
+    const bool wanted = (want >> ln) & 1;
+    // a wanted lane's place among them, and the lane at each place
+    const int place = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(want >> 32),
+                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)want, 0u));
+    // (the others push to the places after them, which no tile row reads)
+    const int n = __popcll(want);
+    const int lane_at = __builtin_amdgcn_ds_permute(4 * (wanted ? place : n + ln - place), ln);
     float mine = 0.0f;
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-        if (((want >> (16 * ct)) & 0xFFFFull) == 0) continue;
-        const int src = 16 * ct + r;
+#pragma unroll 1
+    for (int ct = 0; 16 * ct < n; ++ct) {
+        const int src = __shfl(lane_at, 16 * ct + r);
         float v[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -156,7 +178,8 @@ __device__ inline float mlp_wave(const MlpDev& m, const float f[kMlpIn], uint64_
         const bf16x4 xb = split_inputs(v, g);
         f32x4 h1[4], h2[4];
         const float y = mlp_tile(m, xb, h1, h2);
-        if (g == ct) mine = y;
+        const float got = __shfl(y, place & 15);
+        if (wanted && (place >> 4) == ct) mine = got;
     }
     return mine;
 }
