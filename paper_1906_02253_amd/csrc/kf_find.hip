@@ -581,6 +581,58 @@ __device__ inline uint64_t merge_key(int nhits, float c2, int j, int c)
            ((uint64_t)c << 8);
 }
 
+// A 64-bit value of one lane (uniform), of the lane before (0 in a row's
+// first), and the wave's smallest 32-bit value (uniform).
+__device__ inline uint64_t readlane64(uint64_t v, int lane)
+{
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), lane) << 32) |
+           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+}
+
+__device__ inline uint64_t lane_before64(uint64_t v)
+{
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, 0x111, 0xf, 0xf, false);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), 0x111, 0xf, 0xf, false);
+    return ((uint64_t)hi << 32) | lo;
+}
+
+template <int CTRL, int ROWS>
+__device__ inline uint32_t dpp_min_u32(uint32_t v)
+{
+    const uint32_t u = (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, CTRL, ROWS, 0xf, false);
+    return u < v ? u : v;
+}
+
+__device__ inline uint32_t wave_min_u32(uint32_t v, int lanes)
+{
+    // row shifts by 1, 2, 4, 8, then the rows' last lanes broadcast upwards
+    v = dpp_min_u32<0x111, 0xf>(v);
+    v = dpp_min_u32<0x112, 0xf>(v);
+    v = dpp_min_u32<0x114, 0xf>(v);
+    v = dpp_min_u32<0x118, 0xf>(v);
+    v = dpp_min_u32<0x142, 0xa>(v);
+    v = dpp_min_u32<0x143, 0xc>(v);
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, lanes - 1);
+}
+
+template <int CTRL, int ROWS>
+__device__ inline int dpp_max_i32(int v)
+{
+    const int u = __builtin_amdgcn_update_dpp(v, v, CTRL, ROWS, 0xf, false);
+    return u > v ? u : v;
+}
+
+// running maximum over the lanes
+__device__ inline int wave_max_scan(int v)
+{
+    v = dpp_max_i32<0x111, 0xf>(v);
+    v = dpp_max_i32<0x112, 0xf>(v);
+    v = dpp_max_i32<0x114, 0xf>(v);
+    v = dpp_max_i32<0x118, 0xf>(v);
+    v = dpp_max_i32<0x142, 0xa>(v);
+    return dpp_max_i32<0x143, 0xc>(v);
+}
+
 // The chi2 in a selection key (its float bits made monotone).
 __device__ inline float merge_key_chi2(uint64_t key)
 {
@@ -605,11 +657,95 @@ __device__ inline void load_owner_cov(const C* r, C pc[6])
     }
 }
 
+// A hit (record halves r0: x, y, z, su; r1: sv, cos phi, sin phi, index)
+// against a window owner's record (oa, ob: see WaveLds::orec): inside the
+// window's box.  |azimuth difference| <= dphi (< pi/2): same half-plane, |sin|
+// bounded.
+template <typename T>
+__device__ inline bool window_test(const float4& oa, const float4& ob, const float4& r0, const float4& r1)
+{
+    const float hcp = r1.y, hsp = r1.z;
+    const T ox = T(oa.x), oy = T(oa.y), oz = T(oa.z);
+    const T cpp = T(oa.w), spp = T(ob.x);
+    const T sin_dphi = T(ob.y), wv = T(ob.z);
+    const int fl = __float_as_int(ob.w);
+    const int kind = fl >> 1;
+    bool pass = (fl & 1) || (T(hcp) * cpp + T(hsp) * spp > T(0) &&
+                             !(Tr<T>::abs_(T(hsp) * cpp - T(hcp) * spp) > sin_dphi));
+    if (pass) {
+        const T rv = kind == 0 ? T(r0.z) - oz : T(hcp) * (T(r0.x) - ox) + T(hsp) * (T(r0.y) - oy);
+        pass = !(Tr<T>::abs_(rv) > wv);
+    }
+    return pass;
+}
+
+// Its chi2 against the owner's position and position covariance pc: below the cut.
+template <typename T, typename C, typename U>
+__device__ inline bool chi2_test(const float4& oa, const float4& ob, const C pc[6], const float4& r0,
+                                 const float4& r1, float cut, unsigned* n_chi2, float* c2f)
+{
+    HitFrame<U> f;
+    f.hx = U(r0.x);
+    f.hy = U(r0.y);
+    f.hz = U(r0.z);
+    f.c = U(r1.y);
+    f.s = U(r1.z);
+    f.vu = U(r0.w) * U(r0.w);
+    f.vv = U(r1.x) * U(r1.x);
+    const U c2u = hit_chi2_pos<U>(U(oa.x), U(oa.y), U(oa.z), U(pc[0]), U(pc[1]), U(pc[2]), U(pc[3]), U(pc[4]),
+                                  U(pc[5]), f, __float_as_int(ob.w) >> 1);
+    ++*n_chi2;
+    *c2f = float(c2u);
+    return c2u < U(cut);
+}
+
+// Whether the hit's chi2 can be below `below` (in FP32, to be on the safe
+// side): chi2 >= ru^2 / S00 and >= rv^2 / S11 for any covariance, each residual
+// taken smaller and each variance larger than its rounding can make it.
+__device__ inline bool chi2_may_be_below(const float4& oa, const float4& ob, const float pf[6], const float4& r0,
+                                         const float4& r1, float below)
+{
+    const float c = r1.y, s = r1.z, dx = r0.x - oa.x, dy = r0.y - oa.y;
+    const float slack = 1e-6f * (fabsf(dx) + fabsf(dy));
+    const float pt = 4e-6f * (pf[0] + pf[3]);
+    const float ru = fmaxf(fabsf(c * dy - s * dx) - slack, 0.0f);
+    const float s00 = s * s * pf[0] - 2.0f * s * c * pf[1] + c * c * pf[3] + r0.w * r0.w + pt;
+    float rv, s11;
+    if ((__float_as_int(ob.w) >> 1) == 0) {
+        rv = fabsf(r0.z - oa.z);
+        s11 = pf[5] + r1.x * r1.x;
+    } else {
+        rv = fmaxf(fabsf(c * dx + s * dy) - slack, 0.0f);
+        s11 = c * c * pf[0] + 2.0f * s * c * pf[1] + s * s * pf[3] + r1.x * r1.x + pt;
+    }
+    const float lim = 1.0001f * below;
+    // (a comparison with NaN leaves it to the exact test)
+    return !(ru * ru > lim * s00) && !(rv * rv > lim * s11);
+}
+
 constexpr int kSeg = 128;       // phi rows queued per wave per round
 constexpr int kScanBatch = 4;   // hits per lane in flight in the scan
 constexpr int kAcc = 64 * kScanBatch;
 constexpr int kInsBatch = 4;    // accepted hits an owner loads together
+// Bins from which a window is scanned with its seed's others.  The group scan
+// costs its lists' set-up, and reads the union of windows that may differ; the
+// queue one load per candidate and hit.  64 events of 2100 tracks (128 x 32
+// bins): 2049 us by the queue alone, 1914 from 256 bins on, 1862 from 1024,
+// 1926 from 4096; 16 events with overlapping seeds: 1450, 1232, 1238, 1290.
+constexpr int kLongBins = 1024;
 constexpr int kSelKeys = 64 * (kMaxCands + 1);   // children of a wave's candidates, at most
+
+// Covariance entries beside the position block that a candidate leaves in LDS
+// during the window scan and the selection (their packed indices): they need
+// no registers there, and a surviving child reads them from its parent's
+// column instead of by two shuffles each.  More would cost the eighth wave of
+// a compute unit.
+constexpr int kPark = 8;
+__host__ __device__ constexpr int parked(int k)
+{
+    constexpr int at[kPark] = {pk(0, 3), pk(0, 4), pk(0, 5), pk(1, 3), pk(1, 4), pk(1, 5), pk(2, 3), pk(2, 4)};
+    return at[k];
+}
 
 // LDS of one wave; arrays lane-minor unless noted.  The window scan's queues
 // and the selection's keys are never live together.
@@ -617,6 +753,7 @@ template <typename C>
 struct alignas(16) WaveLds {
     C ocov[64 * kOwnCov<C>];    // window owner's predicted position covariance
                                 //          P00 P01 P02 P11 P12 P22 (16-byte rows)
+    C park[kPark * 64];         // entries of the covariance that wait here for the selection
     float orec[64 * 8];         // window owner record: predicted x, y, z, cos and sin of its
                                 //        azimuth, sin(dphi), wv, flags (two 16-byte reads)
     union {
@@ -648,6 +785,174 @@ template <typename C>
 __host__ __device__ inline size_t find_shared_bytes(int W, int nl)
 {
     return find_layers_bytes(nl) + sizeof(WaveLds<C>) * ((W + 63) / 64);
+}
+
+// wave-wide exclusive prefix sum (and total) of one int per lane
+__device__ inline int wave_scan(int v, int wlanes, int* total)
+{
+    const int ln = (int)(threadIdx.x & 63);
+    int incl = v;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int u = __shfl_up(incl, o);
+        if (ln >= o) incl += u;
+    }
+    *total = __shfl(incl, wlanes - 1);
+    return incl - v;
+}
+
+// prefix of nseg queued rows' hit counts, two rows per lane; the total
+template <typename LEN, typename PRE>
+__device__ inline int row_prefix(LEN len, PRE pre, int nseg, int wlanes)
+{
+    const int ln = (int)(threadIdx.x & 63);
+    const int la = 2 * ln < nseg ? len[2 * ln] : 0;
+    const int lb = 2 * ln + 1 < nseg ? len[2 * ln + 1] : 0;
+    int H = 0;
+    const int p = wave_scan(la + lb, wlanes, &H);
+    if (2 * ln < nseg) pre[2 * ln] = p;
+    if (2 * ln + 1 < nseg) pre[2 * ln + 1] = p + la;
+    if (ln == 0) pre[nseg] = H;
+    wave_fence();
+    return H;
+}
+
+// Scan of the long windows of a seed's candidates on one layer (the lanes of
+// `group`, at most an eighth of the wave's): rows u_lo .. u_lo + u_rows - 1
+// (modulo np) times second bins u_v0 .. u_v1 of the layer whose first bin in
+// the event is row0, the union of the windows.  64 consecutive hits at a time
+// are tested against each window; the windows' best hits are sorted lists over
+// eight lanes each, which only hits below a list's entry MC - 1 enter, best
+// first.  A function of its own: the finding kernel has no registers to spare
+// for it, and it runs for a few seeds in a thousand.
+struct LongList {
+    uint64_t best;      // lane 8 k + q: entry q of the k-th window
+    int bi;             // its binned index
+    int count;          // lanes 8 k ..: hits below the cut in the k-th window (all of them until
+                        // there are MC)
+    unsigned tests;     // chi2 tests of this lane
+};
+
+template <typename C>
+using LdsPtr = __attribute__((address_space(3))) WaveLds<C>*;
+
+template <typename T, typename C, typename U>
+__device__ __attribute__((noinline)) LongList long_scan(LdsPtr<C> w, const BinnedHit* bh, const int32_t* bin_off,
+                                                        uint64_t group_, int u_lo_, int u_rows_, int u_v0_,
+                                                        int u_v1_, int np_, int n2_, int row0_, int MC_,
+                                                        int wlanes_, float cut)
+{
+    // (arguments arrive in vector registers; these are uniform)
+    auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    const int u_lo = uni(u_lo_), u_rows = uni(u_rows_), u_v0 = uni(u_v0_), u_v1 = uni(u_v1_);
+    const int np = uni(np_), n2 = uni(n2_), row0 = uni(row0_), MC = uni(MC_), wlanes = uni(wlanes_);
+    const uint64_t group = ((uint64_t)(uint32_t)uni((int)(group_ >> 32)) << 32) | (uint32_t)uni((int)(uint32_t)group_);
+    const int ln = (int)(threadIdx.x & 63);
+    auto* h0s = w->seg + kSeg;
+    auto* lens = w->seg + 2 * kSeg;
+    auto* pre = w->segpre;
+    auto* mark = w->acc;
+    LongList L{~0ull, -1, 0, 0u};
+    const int segcap = 2 * wlanes < kSeg ? 2 * wlanes : kSeg;
+    for (int rr0 = 0; rr0 < u_rows; rr0 += segcap) {
+        const int nseg = u_rows - rr0 < segcap ? u_rows - rr0 : segcap;
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const int j = r * wlanes + ln;
+            if (j < nseg) {
+                const int bb = u_lo + rr0 + j;
+                const int rb = row0 + (((bb % np) + np) % np) * n2;
+                const int h0 = bin_off[rb + u_v0];
+                const int h1 = bin_off[rb + u_v1 + 1];
+                h0s[j] = h0;
+                lens[j] = h1 - h0;
+            }
+        }
+        wave_fence();
+        const int H = uni(row_prefix(lens, pre, nseg, wlanes));
+        int row_at = 0;                     // the row of the batch's first hit, or before it
+        for (int g0 = 0; g0 < H; g0 += wlanes * kScanBatch) {
+            float4 r0[kScanBatch], r1[kScanBatch];
+            int bix[kScanBatch];
+            // the row of each hit: rows that start in the batch leave their number
+            // at their first hit, and a running maximum carries it on
+#pragma unroll
+            for (int q = 0; q < kScanBatch; ++q) mark[q * wlanes + ln] = row_at;
+            wave_fence();
+            for (int r = row_at + 1 + ln; __ballot(r < nseg); r += wlanes) {
+                const int p0 = r < nseg ? pre[r] : 0x7fffffff;
+                if (p0 < g0 + wlanes * kScanBatch && p0 >= g0 && pre[r + 1] > p0) mark[p0 - g0] = r;
+            }
+            wave_fence();
+#pragma unroll
+            for (int q = 0; q < kScanBatch; ++q) {
+                const int g = g0 + q * wlanes + ln;
+                int row = wave_max_scan(mark[q * wlanes + ln]);
+                row = row > row_at ? row : row_at;
+                row_at = __builtin_amdgcn_readlane(row, wlanes - 1);
+                bix[q] = g < H ? h0s[row] - pre[row] + g : -1;
+                const int b = bix[q] < 0 ? 0 : bix[q];
+                r0[q] = *(const float4*)&bh[b].x;
+                r1[q] = *(const float4*)&bh[b].sv;
+            }
+            int k = 0;
+            for (uint64_t g = group; g; g &= g - 1, ++k) {
+                const int l = __builtin_ctzll(g);
+                float rec[8];
+                C pc[6];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) rec[q] = w->orec[l * 8 + q];
+#pragma unroll
+                for (int q = 0; q < 6; ++q) pc[q] = w->ocov[l * kOwnCov<C> + q];
+                const float4 oa = make_float4(rec[0], rec[1], rec[2], rec[3]);
+                const float4 ob = make_float4(rec[4], rec[5], rec[6], rec[7]);
+                float pf[6];
+#pragma unroll
+                for (int q = 0; q < 6; ++q) pf[q] = float(pc[q]);
+                const bool mine = ln >> 3 == k;
+                uint64_t kth = readlane64(L.best, 8 * k + MC - 1);
+#pragma unroll
+                for (int q = 0; q < kScanBatch; ++q) {
+                    // the exact chi2 only of hits that may enter the list; the others
+                    // matter no more once it is full (count says whether it is)
+                    float c2f = 0.0f;
+                    const bool in = bix[q] >= 0 && window_test<T>(oa, ob, r0[q], r1[q]);
+                    L.tests += in ? 1 : 0;
+                    const float below = kth == ~0ull ? __uint_as_float(0x7f800000u) : fmaxf(child_key_chi2(kth), 1e-3f);
+                    bool ok = in && chi2_may_be_below(oa, ob, pf, r0[q], r1[q], below);
+                    if (__ballot(ok) == 0) continue;
+                    unsigned counted = 0;
+                    if (ok) ok = chi2_test<T, C, U>(oa, ob, pc, r0[q], r1[q], cut, &counted, &c2f);
+                    const int n_ok = __popcll(__ballot(ok));
+                    L.count += mine ? n_ok : 0;
+                    uint64_t e = ok ? child_key(c2f, __float_as_int(r1[q].w)) : ~0ull;
+                    // the best remaining hit, by its key's high word (by the low one
+                    // among equals), until none is below the last entry
+                    while (__ballot(e < kth)) {
+                        const uint32_t hi = wave_min_u32((uint32_t)(e >> 32), wlanes);
+                        uint64_t at = __ballot((uint32_t)(e >> 32) == hi);
+                        if (at & (at - 1)) {
+                            const uint32_t lo = wave_min_u32((uint32_t)(e >> 32) == hi ? (uint32_t)e : ~0u, wlanes);
+                            at = __ballot((uint32_t)(e >> 32) == hi && (uint32_t)e == lo);
+                        }
+                        const int from = __builtin_ctzll(at);
+                        const uint64_t ee = readlane64(e, from);
+                        const int e_bi = __builtin_amdgcn_readlane(bix[q], from);
+                        // the lane before's entry (a list's first: below everything)
+                        uint64_t up = lane_before64(L.best);
+                        up = (ln & 7) ? up : 0;
+                        const int up_bi = __builtin_amdgcn_update_dpp(0, L.bi, 0x111, 0xf, 0xf, false);
+                        const bool here = mine && ee < L.best, before = ee < up;
+                        L.best = here ? (before ? up : ee) : L.best;
+                        L.bi = here ? (before ? up_bi : e_bi) : L.bi;
+                        kth = readlane64(L.best, 8 * k + MC - 1);
+                        if (ln == from) e = ~0ull;
+                    }
+                }
+            }
+        }
+        wave_fence();                       // the queue is rewritten next
+    }
+    return L;
 }
 
 // waves per SIMD the register allocation is held to (a build-time tuning knob)
@@ -906,6 +1211,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
                 oc[3] = P[pk(1, 1)];
                 oc[4] = P[pk(1, 2)];
                 oc[5] = P[pk(2, 2)];
+#pragma unroll
+                for (int k = 0; k < kPark; ++k) w.park[k * 64 + ln64] = P[parked(k)];
             }
             // this candidate's accepted hits, best first: key and binned index
             uint64_t lk[kMaxCands];
@@ -961,22 +1268,76 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
                 int32_t* ac_id = ac_first + kAcc;
                 int32_t* ac_bi = ac_id + kAcc;
                 float* ac_c2 = w.accc2;
-                // wave-wide exclusive prefix sum (and total) of one int per lane
-                auto wave_scan = [&](int v, int* total) {
-                    int incl = v;
-                    for (int o = 1; o < 64; o <<= 1) {
-                        const int u = __shfl_up(incl, o);
-                        if (ln >= o) incl += u;
+                const int segcap = 2 * wlanes < kSeg ? 2 * wlanes : kSeg;
+                // (0) windows of kLongBins bins or more, first: the candidates of one
+                // seed on one layer look at nearly the same hits, so the union of
+                // their windows is read once, 64 consecutive hits at a time, and
+                // every hit is tested against each of them.  Their best hits are
+                // sorted lists over eight lanes each, which a hit enters at once, and
+                // only the hits below a list's last entry do, best first.  A few
+                // low-pT seeds of a large event test 30,000 to 60,000 hits; by the
+                // queue below their hits were loaded once per candidate, 256 at a
+                // time and waited for, and inserted one by one by the owner lane:
+                // 15 to 20 ns a hit, and the longest such seed, 1.2 ms of its own,
+                // ended the pass (16 events with overlapping seeds: 1450 us, now
+                // 1238).  Steered kernels keep to the queue: with the call they
+                // took 661 us for 24 events, without 649.
+                uint64_t longs = 0;
+                if constexpr (!STEER) longs = __ballot(pl >= 0 && (int64_t)nrow * (v1 - v0 + 1) >= kLongBins);
+                if (__builtin_expect_with_probability(longs != 0, 0, 0.999))
+                while (longs) {
+                    const int o = __builtin_ctzll(longs);
+                    const int o_pl = __builtin_amdgcn_readlane(pl, o);
+                    const int o_base = __builtin_amdgcn_readlane(lbase, o);
+                    // the group: this seed's long windows on this layer, eight lanes each
+                    uint64_t group = longs & __ballot(pl == o_pl && lbase == o_base);
+                    while (__popcll(group) > wlanes / 8) group &= ~(1ull << (63 - __builtin_clzll(group)));
+                    longs &= ~group;
+                    int u_lo = 0x7fffffff, u_hi = -0x7fffffff, u_v0 = 0x7fffffff, u_v1 = 0;
+                    for (uint64_t g = group; g; g &= g - 1) {
+                        const int l = __builtin_ctzll(g);
+                        const int r_lo = __builtin_amdgcn_readlane(row_lo, l);
+                        const int r_hi = r_lo + __builtin_amdgcn_readlane(nrow, l) - 1;
+                        const int b0 = __builtin_amdgcn_readlane(v0, l), b1 = __builtin_amdgcn_readlane(v1, l);
+                        u_lo = r_lo < u_lo ? r_lo : u_lo;
+                        u_hi = r_hi > u_hi ? r_hi : u_hi;
+                        u_v0 = b0 < u_v0 ? b0 : u_v0;
+                        u_v1 = b1 > u_v1 ? b1 : u_v1;
                     }
-                    *total = __shfl(incl, wlanes - 1);
-                    return incl - v;
-                };
+                    const int o_np = __builtin_amdgcn_readlane(np, o), o_n2 = __builtin_amdgcn_readlane(n2, o);
+                    const int o_row0 = __builtin_amdgcn_readlane(row0, o);
+                    int u_rows = u_hi - u_lo + 1;
+                    if (u_rows >= o_np || u_rows <= 0) {
+                        u_lo = 0;
+                        u_rows = o_np;
+                    }
+                    const LongList ll = long_scan<T, C, U>(
+                        (LdsPtr<C>)(&w), a.bh, a.bin_off, group, u_lo, u_rows, u_v0, u_v1, o_np, o_n2, o_row0,
+                        MC, wlanes, cut);
+                    n_chi2 += ll.tests;
+                    int k = 0;
+                    for (uint64_t g = group; g; g &= g - 1, ++k) {
+                        const int l = __builtin_ctzll(g);
+                        const int n_acc = __builtin_amdgcn_readlane(ll.count, 8 * k);
+                        if (ln == l) {
+                            nacc = n_acc;
+                            nrow = 0;                       // nothing left for the queue
+                        }
+#pragma unroll
+                        for (int q = 0; q < kMaxCands; ++q) {
+                            const uint64_t x = readlane64(ll.best, 8 * k + q);
+                            const int z = __builtin_amdgcn_readlane(ll.bi, 8 * k + q);
+                            lk[q] = ln == l ? x : lk[q];
+                            lbi[q] = ln == l ? z : lbi[q];
+                        }
+                    }
+                }
                 // rows of every lane, flattened: lane o owns rows [rowpre[o],
                 // rowpre[o] + nrow_o) of the wave's row list
                 ac_first[ln] = 0x7fffffff;
                 ac_last[ln] = -1;
                 int R = 0;
-                const int rpre = wave_scan(nrow, &R);
+                const int rpre = wave_scan(nrow, wlanes, &R);
                 // the row parameters of each owner, for the lanes that expand its rows
                 int32_t* rw_par = w.rowp;
                 rw_par[ln] = rpre;
@@ -985,7 +1346,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
                 rw_par[192 + ln] = row0;
                 rw_par[256 + ln] = np | (n2 << 16);
                 wave_fence();
-                const int segcap = 2 * wlanes < kSeg ? 2 * wlanes : kSeg;
                 for (int rr0 = 0; rr0 < R; rr0 += segcap) {
                     // (1) queue rows rr0 .. rr0 + segcap - 1, two per lane; their bin
                     //     ranges are loaded together
@@ -1015,14 +1375,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
                     }
                     wave_fence();
                     // (2) prefix of the queued rows' hit counts, two rows per lane
-                    const int la = 2 * ln < nseg ? sg_len[2 * ln] : 0;
-                    const int lb = 2 * ln + 1 < nseg ? sg_len[2 * ln + 1] : 0;
-                    int H = 0;
-                    const int pre = wave_scan(la + lb, &H);
-                    if (2 * ln < nseg) sg_pre[2 * ln] = pre;
-                    if (2 * ln + 1 < nseg) sg_pre[2 * ln + 1] = pre + la;
-                    if (ln == 0) sg_pre[nseg] = H;
-                    wave_fence();
+                    const int H = row_prefix(sg_len, sg_pre, nseg, wlanes);
                     // (3) the flattened hits, 64 x kScanBatch per round.  Lane ln
                     //     walks its own contiguous segment of the list, kScanBatch
                     //     hits per round, so that a round holds hits of many owners
@@ -1075,41 +1428,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
                             float c2f = 0.0f;
                             const int o = own[q];
                             if (o >= 0) {
-                                const float hcp = r1[q].y, hsp = r1[q].z;
                                 const float4 oa = *(const float4*)&w.orec[o * 8];
                                 const float4 ob = *(const float4*)&w.orec[o * 8 + 4];
-                                const T ox = T(oa.x), oy = T(oa.y), oz = T(oa.z);
-                                const T cpp = T(oa.w), spp = T(ob.x);
-                                const T sin_dphi = T(ob.y), wv = T(ob.z);
-                                const int fl = __float_as_int(ob.w);
-                                const int kind = fl >> 1;
-                                // |azimuth difference| <= dphi (< pi/2): same half-plane, |sin| bounded
-                                bool pass = (fl & 1) || (T(hcp) * cpp + T(hsp) * spp > T(0) &&
-                                                         !(Tr<T>::abs_(T(hsp) * cpp - T(hcp) * spp) >
-                                                           sin_dphi));
-                                if (pass) {
-                                    const T rv = kind == 0 ? T(r0[q].z) - oz
-                                                           : T(hcp) * (T(r0[q].x) - ox) +
-                                                                 T(hsp) * (T(r0[q].y) - oy);
-                                    pass = !(Tr<T>::abs_(rv) > wv);
-                                }
-                                if (pass) {
-                                    HitFrame<U> f;
-                                    f.hx = U(r0[q].x);
-                                    f.hy = U(r0[q].y);
-                                    f.hz = U(r0[q].z);
-                                    f.c = U(hcp);
-                                    f.s = U(hsp);
-                                    f.vu = U(r0[q].w) * U(r0[q].w);
-                                    f.vv = U(r1[q].x) * U(r1[q].x);
+                                if (window_test<T>(oa, ob, r0[q], r1[q])) {
                                     C pc[6];
                                     load_owner_cov(w.ocov + o * kOwnCov<C>, pc);
-                                    const U c2u = hit_chi2_pos<U>(U(ox), U(oy), U(oz), U(pc[0]), U(pc[1]),
-                                                                  U(pc[2]), U(pc[3]), U(pc[4]), U(pc[5]),
-                                                                  f, kind);
-                                    ++n_chi2;
-                                    ok = c2u < U(cut);
-                                    c2f = float(c2u);
+                                    ok = chi2_test<T, C, U>(oa, ob, pc, r0[q], r1[q], cut, &n_chi2, &c2f);
                                 }
                             }
                             okq[q] = ok;
@@ -1266,10 +1590,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
                     src = lbase + sel_j;
                 }
             }
+            {
+                // position and its covariance from the parent's owner record, the
+                // parked entries, and the rest from its registers
+                C pc[6];
+                load_owner_cov(w.ocov + src * kOwnCov<C>, pc);
+                const float4 x = *(const float4*)&w.orec[src * 8];
+                p[0] = T(x.x);
+                p[1] = T(x.y);
+                p[2] = T(x.z);
 #pragma unroll
-            for (int k = 0; k < 6; ++k) p[k] = __shfl(p[k], src);
+                for (int k = 3; k < 6; ++k) p[k] = __shfl(p[k], src);
+                P[pk(0, 0)] = pc[0];
+                P[pk(0, 1)] = pc[1];
+                P[pk(0, 2)] = pc[2];
+                P[pk(1, 1)] = pc[3];
+                P[pk(1, 2)] = pc[4];
+                P[pk(2, 2)] = pc[5];
 #pragma unroll
-            for (int k = 0; k < 21; ++k) P[k] = __shfl(P[k], src);
+                for (int k = 0; k < kPark; ++k) P[parked(k)] = w.park[k * 64 + src];
+                P[pk(2, 5)] = __shfl(P[pk(2, 5)], src);
+#pragma unroll
+                for (int k = pk(3, 3); k < 21; ++k) P[k] = __shfl(P[k], src);
+            }
             nhits = __shfl(nhits, src);
             misses = __shfl(misses, src);
             status = __shfl(status, src);
