@@ -148,7 +148,7 @@ int prepare_find(kf_ctx* ctx, const kf_hits* hits, const int32_t* event_off, int
     if ((int64_t)n_events * per_event >= 0x7fffffffLL ||
         (int64_t)n_events * 4096 >= 0x7fffffffLL)
         return fail(ctx, KF_EINVAL, "%s: n_events x bins per event exceeds 2^31", what);
-    pl.bl.per_event = (int32_t)per_event;
+    pl.bl.per_event = (int32_t)per_event + 1;
     const size_t lds = kfmi::find_shared_size(W, nl, prec);
     if (ctx->max_lds > 0 && lds > (size_t)ctx->max_lds)
         return fail(ctx, KF_EUNSUPPORTED, "%s: width %d needs %zu bytes of LDS, device allows %d",
@@ -251,8 +251,8 @@ int prepare_find(kf_ctx* ctx, const kf_hits* hits, const int32_t* event_off, int
 
 hipError_t phase_bin(const kf_ctx* ctx, const kfmi::FindLaunch& L, hipStream_t s)
 {
-    return kfmi::launch_bin(L.pl, L.hits, L.event_off, (int)L.n_events, ctx->d_layers,
-                            ctx->n_layers, s);
+    return kfmi::launch_bin(L.pl, L.hits, L.event_off, (int)L.n_events, ctx->layers,
+                            ctx->d_layers, ctx->n_layers, s);
 }
 
 hipError_t phase_order(const kf_ctx* ctx, const kfmi::FindLaunch& L, hipStream_t s)

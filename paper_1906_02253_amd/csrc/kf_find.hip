@@ -1,6 +1,6 @@
 // Combinatorial track finding on gfx950.
 //
-//   a1  bin hits per (event, layer, phi bin, z|r bin): count, scan, scatter
+//   a1  bin hits per (event, layer, phi bin, z|r bin): counting sorts
 //       into 32-byte records (paper Sec. 3.2: hits handed in by the caller;
 //       binning makes the per-layer hit search a contiguous range scan);
 //   a2  order seeds by (event, eta bin, phi bin), events optionally largest
@@ -80,17 +80,278 @@ __device__ inline int block_scan_excl(int v, int* total, int* lds)
     return woff + incl - v;
 }
 
-// Hits are binned in two levels of counting sort, all hot counters in LDS:
-// (1) group hits by segment = (event, layer): a workgroup histograms a chunk
-//     of hits in LDS and reserves each segment's share with one global
-//     atomic, then scatters the hit indices;
-// (2) one workgroup per segment counts its hits per (phi, z|r) bin in LDS,
-//     scans the counts into the segment's bin offsets and writes the 32-byte
-//     records contiguously.
-constexpr int kSegChunk = 4096;      // hits per workgroup in level 1
+// Hits are binned in one of two ways.  A few (bin_direct) in one launch of
+// one workgroup, or a few, per (event, layer): it streams the layer numbers of
+// its event, lists its layer's hits, counts them per (phi, z|r) bin in LDS,
+// scans the counts into the layer's bin offsets and writes the 32-byte records
+// in bin order.  The hits below its layer, counted in the same stream, give its
+// first record, so no workgroup waits for another.  More hits go through two
+// levels of counting sort (below): there the stream, once per layer, and the
+// gathers, which use a few bytes of every line n_layers times over, cost more
+// than seven launches and writing each record twice.  A pass by the one launch
+// and by the two levels: one event of 4200 hits 197 and 220 us, of 56,000 241
+// and 246, of 140,000 327 and 311; four of 56,000 378 and 331; thirty of 6800
+// 312 and 326, ten of 20,400 397 and 404.
+inline bool bin_direct(int64_t n_hits, int n_events)
+{
+    return n_hits <= 65536 || (n_hits <= 262144 && n_hits <= (int64_t)n_events * 24576);
+}
+constexpr int kDirectShare = 1024;  // hits that a workgroup writes, on average, at least
+constexpr int kDirectSplit = 8;     // workgroups of an (event, layer), at most
+constexpr int kBinThreads = 1024;
+constexpr int kBinWaves = kBinThreads / 64;
+constexpr int kBinStream = 8;       // layer numbers a lane loads together
+constexpr int kBinBatch = 3;        // hits of a lane whose positions are gathered together
+constexpr int kBinItems = 15;       // listed hits of a lane, at most, in LDS
+constexpr int kBinCap = kBinItems * kBinThreads;   // with 4096 bins, two workgroups share a CU
+
+// first phi row of share s of a layer's np rows; the share of row b is b * split / np
+__host__ __device__ inline int share_row(int s, int np, int split) { return (s * np + split - 1) / split; }
+
+__device__ inline int row_bin(const kf_layer& L, int bp, float hx, float hy, float hz)
+{
+    const float v = L.kind == 0 ? hz : sqrtf(hx * hx + hy * hy);
+    return bp * L.nbin_2 + coord_bin_of(v, float(L.lo), float(L.hi), L.nbin_2);
+}
+
+__device__ inline int hit_bin(const kf_layer& L, float hx, float hy, float hz)
+{
+    return row_bin(L, phi_bin_of(atan2f(hy, hx), L.nbin_phi), hx, hy, hz);
+}
+
+struct HitView {
+    const float *x, *y, *z, *su, *sv;
+    const int32_t* layer;
+};
+
+__device__ inline BinnedHit binned_record(const HitView& h, int32_t i)
+{
+    BinnedHit r;
+    r.x = h.x[i];
+    r.y = h.y[i];
+    r.z = h.z[i];
+    r.su = h.su[i];
+    r.sv = h.sv[i];
+    r.idx = i;
+    const float rho = sqrtf(r.x * r.x + r.y * r.y);
+    r.cphi = r.x / rho;
+    r.sphi = r.y / rho;
+    return r;
+}
+
+// Streams layer[lo, hi): f(number in the list, hit) for every hit of layer l,
+// in any order; *cnt (LDS, zero on entry) counts them.  Returns this lane's
+// hits of lower layers.
+template <typename F>
+__device__ inline int stream_layer(const int32_t* __restrict__ layer, uint32_t lo, uint32_t hi, int l,
+                                   int* cnt, F f)
+{
+    const int ln = threadIdx.x & 63;
+    int less = 0;
+    for (uint32_t i0 = lo; i0 < hi; i0 += kBinStream * kBinThreads) {
+        int v[kBinStream];
+#pragma unroll
+        for (int q = 0; q < kBinStream; ++q) {
+            const uint32_t i = i0 + q * kBinThreads + threadIdx.x;
+            v[q] = i < hi ? layer[i] : -1;
+        }
+        uint64_t m[kBinStream];
+        int c = 0;
+#pragma unroll
+        for (int q = 0; q < kBinStream; ++q) {
+            m[q] = __ballot(v[q] == l);
+            c += __popcll(m[q]);
+            less += (uint32_t)v[q] < (uint32_t)l ? 1 : 0;
+        }
+        if (c == 0) continue;
+        int base = 0;
+        if (ln == 0) base = atomicAdd(cnt, c);
+        base = __builtin_amdgcn_readfirstlane(base);
+#pragma unroll
+        for (int q = 0; q < kBinStream; ++q) {
+            if (v[q] == l)
+                f(base + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m[q] >> 32),
+                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)m[q], 0u)),
+                  (int32_t)(i0 + q * kBinThreads + threadIdx.x));
+            base += __popcll(m[q]);
+        }
+    }
+    return less;
+}
+
+__global__ __launch_bounds__(kBinThreads) void bin_kernel(
+    HitView h, int64_t n_hits, const int32_t* __restrict__ event_off, int n_events, int stride,
+    int split, const kf_layer* __restrict__ layers, int n_layers, int nb_max, BinLayout bl, int32_t* list_g,
+    int32_t* bin_g, int32_t* perm_g, int32_t* __restrict__ bin_off, BinnedHit* __restrict__ out)
+{
+    extern __shared__ int bin_smem[];
+    int* hist = bin_smem;                 // [nb_max]
+    int* list = bin_smem + nb_max;        // [kBinCap]
+    __shared__ int lds[kBinWaves];
+    __shared__ int cnt[2];
+    const int t = threadIdx.x;
+    // the workgroups of one event on one XCD (workgroups go to the XCDs in turn)
+    const int turn = blockIdx.x / stride, share = turn % split, l = turn / split % n_layers;
+    const int e = (int)(blockIdx.x % stride) + stride * (turn / split / n_layers);
+    if (e >= n_events) return;
+    const kf_layer& L = layers[l];
+    int first = share_row(share, L.nbin_phi, split) * L.nbin_2;
+    int nb = share_row(share + 1, L.nbin_phi, split) * L.nbin_2 - first;
+    // (offsets outside the hits, or that decrease, leave an event without hits)
+    const int64_t o0 = event_off[e], o1 = event_off[e + 1];
+    const uint32_t lo = (uint32_t)(o0 < 0 ? 0 : (o0 < n_hits ? o0 : n_hits));
+    const uint32_t hi = (uint32_t)(o1 < (int64_t)lo ? (int64_t)lo : (o1 < n_hits ? o1 : n_hits));
+    for (int b = t; b < nb_max; b += kBinThreads) hist[b] = 0;
+    if (t < 2) cnt[t] = 0;
+    __syncthreads();
+    const int less = stream_layer(h.layer, lo, hi, l, &cnt[0], [&](int k, int32_t i) {
+        if (k < kBinCap) list[k] = i;
+    });
+    int before;                           // the layer's first record
+    (void)block_scan_excl(less, &before, lds);   // (its barriers cover list and cnt)
+    before += (int)lo;
+    const int n = cnt[0];
+    const bool in_lds = n <= kBinCap;
+    uint32_t place[kBinItems];            // bin, and rank in it; ~0 in another share
+    int lower = 0;                        // this lane's hits in the shares before
+    if (in_lds) {
+#pragma unroll
+        for (int q0 = 0; q0 < kBinItems; q0 += kBinBatch) {
+            if (q0 * kBinThreads >= n) break;
+            float px[kBinBatch], py[kBinBatch], pz[kBinBatch];
+#pragma unroll
+            for (int q = 0; q < kBinBatch; ++q) {
+                const int k = (q0 + q) * kBinThreads + t;
+                const int i = list[k < n ? k : 0];
+                px[q] = h.x[i];
+                py[q] = h.y[i];
+                pz[q] = L.kind == 0 ? h.z[i] : 0.0f;
+            }
+#pragma unroll
+            for (int q = 0; q < kBinBatch; ++q) {
+                place[q0 + q] = ~0u;
+                if ((q0 + q) * kBinThreads + t < n) {
+                    const int b = hit_bin(L, px[q], py[q], pz[q]) - first;
+                    if (b >= 0 && b < nb) place[q0 + q] = ((uint32_t)b << 16) | (uint32_t)atomicAdd(&hist[b], 1);
+                    lower += b < 0 ? 1 : 0;
+                }
+            }
+        }
+    } else {
+        // too many for the LDS: the first share's workgroup takes the layer
+        if (share != 0) return;
+        nb = L.nbin_phi * L.nbin_2;
+        stream_layer(h.layer, lo, hi, l, &cnt[1], [&](int k, int32_t i) { list_g[before + k] = i; });
+        __syncthreads();
+        for (int k = t; k < n; k += kBinThreads) {
+            const int i = list_g[before + k];
+            const int b = hit_bin(L, h.x[i], h.y[i], h.z[i]);
+            atomicAdd(&hist[b], 1);
+            bin_g[before + k] = b;
+        }
+    }
+    int skip;
+    (void)block_scan_excl(lower, &skip, lds);    // (its barriers cover hist)
+    before += skip;
+    // exclusive scan of the bin counts: lane t takes bins [t*per, (t+1)*per)
+    const int per = (nb + kBinThreads - 1) / kBinThreads;
+    const int b0 = t * per;
+    int s = 0;
+    for (int q = 0; q < per; ++q)
+        if (b0 + q < nb) s += hist[b0 + q];
+    int tot;
+    int run = block_scan_excl(s, &tot, lds);
+    int32_t* bo = bin_off + (int64_t)e * bl.per_event + bl.base[l] + first;
+    for (int q = 0; q < per; ++q)
+        if (b0 + q < nb) {
+            const int c = hist[b0 + q];
+            hist[b0 + q] = run;
+            bo[b0 + q] = before + run;
+            run += c;
+        }
+    // the event's last bin ends at an entry of its own
+    if (l == n_layers - 1 && first + nb == L.nbin_phi * L.nbin_2 && t == 0) bo[nb] = before + tot;
+    // the hits in bin order, written so that every line is filled at once
+    int item[kBinItems];
+    if (in_lds) {
+#pragma unroll
+        for (int q = 0; q < kBinItems; ++q) {
+            if (q * kBinThreads >= n) break;
+            const int k = q * kBinThreads + t;
+            item[q] = k < n ? list[k] : 0;
+        }
+    }
+    __syncthreads();
+    if (in_lds) {
+#pragma unroll
+        for (int q = 0; q < kBinItems; ++q) {
+            if (q * kBinThreads >= n) break;
+            if (place[q] != ~0u) list[hist[place[q] >> 16] + (int)(place[q] & 0xFFFFu)] = item[q];
+        }
+        __syncthreads();
+        for (int j0 = t; j0 < tot; j0 += kBinBatch * kBinThreads) {
+            BinnedHit r[kBinBatch];
+#pragma unroll
+            for (int q = 0; q < kBinBatch; ++q) {
+                const int j = j0 + q * kBinThreads;
+                r[q] = binned_record(h, list[j < tot ? j : j0]);
+            }
+#pragma unroll
+            for (int q = 0; q < kBinBatch; ++q)
+                if (j0 + q * kBinThreads < tot) out[before + j0 + q * kBinThreads] = r[q];
+        }
+    } else {
+        for (int k = t; k < n; k += kBinThreads)
+            perm_g[before + atomicAdd(&hist[bin_g[before + k]], 1)] = list_g[before + k];
+        __syncthreads();
+        for (int j = t; j < n; j += kBinThreads) out[before + j] = binned_record(h, perm_g[before + j]);
+    }
+}
+
+// Two levels of counting sort, all hot counters in LDS.  A segment is a share
+// of the phi rows of one (event, layer), `split` of them a layer.
+// (1) Hits are grouped by segment: a workgroup counts a chunk of hits per
+//     segment in LDS and adds the counts to the segments' (seg_count_kernel);
+//     after their prefix sum, it reserves its chunk's share of every segment
+//     with one atomic, sorts the chunk's hits by segment in LDS and writes
+//     them in that order, so that full lines leave (seg_scatter_kernel).
+// (2) One workgroup per segment reads its hits once, counts them per bin in
+//     LDS, scans the counts into the bin offsets, sorts the hits in LDS and
+//     writes the 32-byte records (bin_segment_kernel).
+// Memory bounds each: 16, 48 and 56 bytes a hit, 37, 103 and 107 us for the
+// 9,200,000 hits of 64 events.  (With complete records written from the
+// registers as they came and gathered again in bin order: 187 and 243 us.)
+constexpr int kSegThreads = 1024;
+constexpr int kSegItems = 4;
+constexpr int kSegChunk = kSegThreads * kSegItems;   // hits per workgroup in level 1
 constexpr int kSegLocal = 2048;      // segments a level-1 workgroup counts in LDS
-constexpr int kChunkEvents = 64;    // events of a chunk whose boundaries level 1 keeps in LDS
-constexpr int kScatterBatch = 4;    // hits per lane whose loads the scatter issues together
+constexpr int kChunkEvents = 64;     // events of a chunk whose boundaries level 1 keeps in LDS
+// (512 x 4: 107 us for the 64 events and 27 for the 2,300,000 hits of sixteen
+// on ten layers; 1024 x 3 112 and 32, 256 x 8 110 and 30)
+constexpr int kSortThreads = 512;
+constexpr int kSortItems = 4;
+constexpr int kSortCap = kSortThreads * kSortItems;   // hits a segment's workgroup holds in LDS
+
+// A hit between the levels.
+struct alignas(8) StagedHit {
+    float x, y, z, su, sv;
+    int32_t idx;
+};
+
+__device__ inline BinnedHit binned_record(const StagedHit& h)
+{
+    BinnedHit r;
+    r.x = h.x;
+    r.y = h.y;
+    r.z = h.z;
+    r.su = h.su;
+    r.sv = h.sv;
+    r.idx = h.idx;
+    const float rho = sqrtf(r.x * r.x + r.y * r.y);
+    r.cphi = r.x / rho;
+    r.sphi = r.y / rho;
+    return r;
+}
 
 __device__ inline int event_clamped(const int32_t* off, int n_events, int64_t i)
 {
@@ -99,20 +360,23 @@ __device__ inline int event_clamped(const int32_t* off, int n_events, int64_t i)
     return event_of(off, n_events, i);
 }
 
-__global__ __launch_bounds__(256) void seg_count_kernel(int64_t n_hits, const int32_t* __restrict__ layer,
+__global__ __launch_bounds__(256) void seg_count_kernel(int64_t n_hits, HitView hv,
                                                         const int32_t* __restrict__ event_off,
-                                                        int n_events, int n_layers,
+                                                        int n_events, const kf_layer* __restrict__ layers,
+                                                        int n_layers, int split,
                                                         int32_t* __restrict__ seg_key,
                                                         int32_t* __restrict__ seg_cnt)
 {
     __shared__ int h[kSegLocal];
     __shared__ int eoff[kChunkEvents + 2];
+    __shared__ int nphi[kMaxLayers];
     const int64_t c0 = (int64_t)blockIdx.x * kSegChunk;
     const int64_t c1 = c0 + kSegChunk < n_hits ? c0 + kSegChunk : n_hits;
     const int e0 = event_clamped(event_off, n_events, c0);
     const int e1 = event_clamped(event_off, n_events, c1 - 1);
-    const int s0 = e0 * n_layers;
-    const int ns = (e1 + 1) * n_layers - s0;
+    const int per = n_layers * split;
+    const int s0 = e0 * per;
+    const int ns = (e1 + 1) * per - s0;
     const bool local = ns > 0 && ns <= kSegLocal;   // ns <= 0 only for a decreasing event_off
     // the chunk's event boundaries in LDS: each hit's event by a short search there
     const bool near = e1 >= e0 && e1 - e0 < kChunkEvents;
@@ -121,31 +385,48 @@ __global__ __launch_bounds__(256) void seg_count_kernel(int64_t n_hits, const in
     const int64_t all_lo = event_off[0], all_hi = event_off[n_events];
     if (local)
         for (int b = threadIdx.x; b < ns; b += blockDim.x) h[b] = 0;
+    for (int l = threadIdx.x; l < n_layers; l += blockDim.x) nphi[l] = layers[l].nbin_phi;
     __syncthreads();
-    for (int64_t i = c0 + threadIdx.x; i < c1; i += blockDim.x) {
-        const int l = layer[i];
-        int key = -1;
-        if (l >= 0 && l < n_layers && i >= all_lo && i < all_hi) {
-            int e;
-            if (near) {
-                int lo = 0, hi = e1 - e0 + 1;
-                while (hi - lo > 1) {
-                    const int mid = (lo + hi) >> 1;
-                    if (eoff[mid] <= i) lo = mid;
-                    else hi = mid;
-                }
-                e = e0 + lo;
-            } else {
-                e = event_of(event_off, n_events, i);
-            }
-            key = e * n_layers + l;
+    for (int64_t i0 = c0 + threadIdx.x; i0 < c1; i0 += (int64_t)kSegItems * blockDim.x) {
+        int lay[kSegItems];
+        float x[kSegItems], y[kSegItems];
+#pragma unroll
+        for (int q = 0; q < kSegItems; ++q) {
+            const int64_t i = i0 + (int64_t)q * blockDim.x;
+            lay[q] = i < c1 ? hv.layer[i] : -1;
+            x[q] = split > 1 && i < c1 ? hv.x[i] : 0.0f;
+            y[q] = split > 1 && i < c1 ? hv.y[i] : 0.0f;
         }
-        seg_key[i] = key;
-        if (key >= 0) {
-            // (a decreasing event_off could put a hit outside the chunk's
-            // event range: such a hit takes the global counter)
-            if (local && (unsigned)(key - s0) < (unsigned)ns) atomicAdd(&h[key - s0], 1);
-            else atomicAdd(&seg_cnt[key], 1);
+#pragma unroll
+        for (int q = 0; q < kSegItems; ++q) {
+            const int64_t i = i0 + (int64_t)q * blockDim.x;
+            if (i >= c1) continue;
+            const int l = lay[q];
+            int key = -1;
+            if (l >= 0 && l < n_layers && i >= all_lo && i < all_hi) {
+                int e;
+                if (near) {
+                    int lo = 0, hi = e1 - e0 + 1;
+                    while (hi - lo > 1) {
+                        const int mid = (lo + hi) >> 1;
+                        if (eoff[mid] <= i) lo = mid;
+                        else hi = mid;
+                    }
+                    e = e0 + lo;
+                } else {
+                    e = event_of(event_off, n_events, i);
+                }
+                key = e * n_layers + l;
+                if (split > 1)
+                    key = key * split + phi_bin_of(atan2f(y[q], x[q]), nphi[l]) * split / nphi[l];
+            }
+            seg_key[i] = key;
+            if (key >= 0) {
+                // (a decreasing event_off could put a hit outside the chunk's
+                // event range: such a hit takes the global counter)
+                if (local && (unsigned)(key - s0) < (unsigned)ns) atomicAdd(&h[key - s0], 1);
+                else atomicAdd(&seg_cnt[key], 1);
+            }
         }
     }
     __syncthreads();
@@ -154,138 +435,169 @@ __global__ __launch_bounds__(256) void seg_count_kernel(int64_t n_hits, const in
             if (h[b]) atomicAdd(&seg_cnt[s0 + b], h[b]);
 }
 
-__device__ inline int hit_bin(const kf_layer& L, float hx, float hy, float hz)
+__global__ __launch_bounds__(kSegThreads) void seg_scatter_kernel(int64_t n_hits, HitView hv,
+                                                                  const int32_t* __restrict__ event_off,
+                                                                  int n_events, int per,
+                                                                  const int32_t* __restrict__ seg_key,
+                                                                  const int32_t* __restrict__ seg_off,
+                                                                  int32_t* __restrict__ seg_left,
+                                                                  StagedHit* __restrict__ staged)
 {
-    const int bp = phi_bin_of(atan2f(hy, hx), L.nbin_phi);
-    const float v = L.kind == 0 ? hz : sqrtf(hx * hx + hy * hy);
-    return bp * L.nbin_2 + coord_bin_of(v, float(L.lo), float(L.hi), L.nbin_2);
-}
-
-// Level 1, second pass: each hit's complete record and its bin within the
-// layer go to the hit's segment, so that level 2 streams contiguous records
-// (the caller's hits may come in any order within an event).
-__global__ __launch_bounds__(256) void seg_scatter_kernel(int64_t n_hits, const float* __restrict__ x,
-                                                          const float* __restrict__ y,
-                                                          const float* __restrict__ z,
-                                                          const float* __restrict__ su,
-                                                          const float* __restrict__ sv,
-                                                          const int32_t* __restrict__ event_off,
-                                                          int n_events, const kf_layer* __restrict__ layers,
-                                                          int n_layers,
-                                                          const int32_t* __restrict__ seg_key,
-                                                          const int32_t* __restrict__ seg_off,
-                                                          int32_t* __restrict__ seg_fill,
-                                                          BinnedHit* __restrict__ seg_rec,
-                                                          int32_t* __restrict__ seg_bin)
-{
-    __shared__ int h[kSegLocal];
-    __shared__ int base[kSegLocal];
-    __shared__ kf_layer sl[kMaxLayers];
+    __shared__ StagedHit rec[kSegChunk];  // the chunk's hits by segment
+    __shared__ int pos[kSegChunk];        // their places in `staged`
+    __shared__ int h[kSegLocal], base[kSegLocal];
+    __shared__ int lds[kSegThreads / 64];
+    const int t = threadIdx.x;
     const int64_t c0 = (int64_t)blockIdx.x * kSegChunk;
     const int64_t c1 = c0 + kSegChunk < n_hits ? c0 + kSegChunk : n_hits;
-    const int s0 = event_clamped(event_off, n_events, c0) * n_layers;
-    const int ns = (event_clamped(event_off, n_events, c1 - 1) + 1) * n_layers - s0;
+    int key[kSegItems], rank[kSegItems];
+    StagedHit r[kSegItems];
+#pragma unroll
+    for (int q = 0; q < kSegItems; ++q) {
+        const int64_t i = c0 + q * kSegThreads + t;
+        key[q] = i < c1 ? seg_key[i] : -1;
+        const int64_t j = i < c1 ? i : c0;
+        r[q].x = hv.x[j];
+        r[q].y = hv.y[j];
+        r[q].z = hv.z[j];
+        r[q].su = hv.su[j];
+        r[q].sv = hv.sv[j];
+        r[q].idx = (int32_t)j;
+    }
+    const int s0 = event_clamped(event_off, n_events, c0) * per;
+    const int ns = (event_clamped(event_off, n_events, c1 - 1) + 1) * per - s0;
     const bool local = ns > 0 && ns <= kSegLocal;   // ns <= 0 only for a decreasing event_off
-    for (int l = threadIdx.x; l < n_layers; l += blockDim.x) sl[l] = layers[l];
     if (local) {
-        for (int b = threadIdx.x; b < ns; b += blockDim.x) h[b] = 0;
+        for (int b = t; b < ns; b += kSegThreads) h[b] = 0;
         __syncthreads();
-        for (int64_t i = c0 + threadIdx.x; i < c1; i += blockDim.x) {
-            const int key = seg_key[i];
-            if (key >= 0 && (unsigned)(key - s0) < (unsigned)ns) atomicAdd(&h[key - s0], 1);
-        }
-        __syncthreads();
-        // reserve this chunk's share of every segment it touches
-        for (int b = threadIdx.x; b < ns; b += blockDim.x) {
-            base[b] = h[b] ? seg_off[s0 + b] + atomicAdd(&seg_fill[s0 + b], h[b]) : 0;
-            h[b] = 0;
-        }
+    }
+#pragma unroll
+    for (int q = 0; q < kSegItems; ++q) {
+        rank[q] = -1;
+        if (key[q] < 0) continue;
+        if (local && (unsigned)(key[q] - s0) < (unsigned)ns)
+            rank[q] = atomicAdd(&h[key[q] - s0], 1);
+        else
+            staged[seg_off[key[q]] + atomicSub(&seg_left[key[q]], 1) - 1] = r[q];
+    }
+    if (!local) return;
+    __syncthreads();
+    // the segments' places in the sorted chunk, lane t those of segments
+    // [2 t, 2 t + 2), and a share of every segment for the chunk
+    static_assert(kSegLocal == 2 * kSegThreads, "two segments a lane");
+    const int b0 = 2 * t;
+    const int n0 = b0 < ns ? h[b0] : 0, n1 = b0 + 1 < ns ? h[b0 + 1] : 0;
+    int n;
+    const int at = block_scan_excl(n0 + n1, &n, lds);
+    if (n0) base[b0] = seg_off[s0 + b0] + atomicSub(&seg_left[s0 + b0], n0) - n0 - at;
+    if (n1) base[b0 + 1] = seg_off[s0 + b0 + 1] + atomicSub(&seg_left[s0 + b0 + 1], n1) - n1 - at - n0;
+    if (b0 < ns) h[b0] = at;
+    if (b0 + 1 < ns) h[b0 + 1] = at + n0;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kSegItems; ++q) {
+        if (rank[q] < 0) continue;
+        const int j = h[key[q] - s0] + rank[q];
+        rec[j] = r[q];
+        pos[j] = base[key[q] - s0] + j;
     }
     __syncthreads();
-    // kScatterBatch hits per lane per round: their loads are issued together
-    for (int64_t i0 = c0 + threadIdx.x; i0 < c1; i0 += (int64_t)kScatterBatch * blockDim.x) {
-        int key[kScatterBatch];
-        BinnedHit r[kScatterBatch];
-#pragma unroll
-        for (int q = 0; q < kScatterBatch; ++q) {
-            const int64_t i = i0 + (int64_t)q * blockDim.x;
-            key[q] = i < c1 ? seg_key[i] : -1;
-            if (key[q] >= 0) {
-                r[q].x = x[i];
-                r[q].y = y[i];
-                r[q].z = z[i];
-                r[q].su = su[i];
-                r[q].sv = sv[i];
-                r[q].idx = (int32_t)i;
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < kScatterBatch; ++q) {
-            if (key[q] < 0) continue;
-            const int k = key[q];
-            const int pos = local && (unsigned)(k - s0) < (unsigned)ns
-                                ? base[k - s0] + atomicAdd(&h[k - s0], 1)
-                                : seg_off[k] + atomicAdd(&seg_fill[k], 1);
-            const float rho = sqrtf(r[q].x * r[q].x + r[q].y * r[q].y);
-            r[q].cphi = r[q].x / rho;
-            r[q].sphi = r[q].y / rho;
-            seg_rec[pos] = r[q];
-            seg_bin[pos] = hit_bin(sl[k % n_layers], r[q].x, r[q].y, r[q].z);
-        }
+    // three lanes a record
+    const uint2* src = (const uint2*)rec;
+    uint2* dst = (uint2*)staged;
+    for (int d = t; d < 3 * n; d += kSegThreads) {
+        const int j = (int)((uint32_t)d / 3u);
+        dst[(int64_t)pos[j] * 3 + (d - 3 * j)] = src[d];
     }
 }
 
-// Level 2: one workgroup per segment sorts its records by bin.  The bin
-// counts are histogrammed and scanned in LDS; then every record's place is
-// drawn from its bin's counter and, for segments of up to kBinSrcCap records,
-// kept as the inverse permutation in LDS, so that the records are written in
-// output order (full lines, one read gathered from the segment's own recent
-// records each) instead of scattered 32-byte writes that leave their lines
-// partly written when the L2 evicts them.  Larger segments scatter directly.
-constexpr int kBinThreads = 1024;
-constexpr int kBinSrcCap = 12288;
-__global__ __launch_bounds__(kBinThreads) void bin_segment_kernel(
-    const int32_t* __restrict__ seg_off, const BinnedHit* __restrict__ seg_rec,
-    const int32_t* __restrict__ seg_bin, const kf_layer* __restrict__ layers, int n_layers,
-    int n_seg, int nb_max, BinLayout bl, int32_t* __restrict__ bin_off, BinnedHit* __restrict__ out)
+// bin of a hit within its share; the share was chosen by the same row
+__device__ inline int share_bin(const kf_layer& L, float x, float y, float z, int first, int nb)
 {
+    const int b = hit_bin(L, x, y, z) - first;
+    return b < 0 ? 0 : (b < nb ? b : nb - 1);
+}
+
+__global__ __launch_bounds__(kSortThreads) void bin_segment_kernel(
+    const int32_t* __restrict__ seg_off, const StagedHit* __restrict__ staged,
+    const kf_layer* __restrict__ layers, int n_layers, int split, BinLayout bl,
+    int32_t* __restrict__ bin_off, BinnedHit* __restrict__ out)
+{
+    __shared__ StagedHit rec[kSortCap];
     extern __shared__ int bin_smem[];
-    int* hist = bin_smem;                 // [nb_max]
-    int* src = bin_smem + nb_max;         // [kBinSrcCap]
-    __shared__ int lds[kBinThreads / 64];
+    int* hist = bin_smem;                 // [the most bins of a segment]
+    __shared__ int lds[kSortThreads / 64];
     const int seg = blockIdx.x;
-    const int e = seg / n_layers, l = seg - e * n_layers;
-    const int nb = layers[l].nbin_phi * layers[l].nbin_2;
-    const int lo = seg_off[seg], hi = seg_off[seg + 1];
+    const int el = seg / split, share = seg - el * split;
+    const int e = el / n_layers, l = el - e * n_layers;
+    const kf_layer& L = layers[l];
+    const int first = share_row(share, L.nbin_phi, split) * L.nbin_2;
+    const int nb = share_row(share + 1, L.nbin_phi, split) * L.nbin_2 - first;
+    const int lo = seg_off[seg], n = seg_off[seg + 1] - lo;
     const int t = threadIdx.x;
-    for (int b = t; b < nb; b += kBinThreads) hist[b] = 0;
+    const bool in_lds = n <= kSortCap;
+    // (the records' three parts as plain pairs: an array of records went to scratch)
+    float2 xy[kSortItems] = {}, zu[kSortItems] = {}, vi[kSortItems] = {};
+    if (in_lds && n > 0) {
+#pragma unroll
+        for (int q = 0; q < kSortItems; ++q) {
+            const float2* p = (const float2*)&staged[lo + (q * kSortThreads + t < n ? q * kSortThreads + t : 0)];
+            xy[q] = p[0];
+            zu[q] = p[1];
+            vi[q] = p[2];
+        }
+    }
+    for (int b = t; b < nb; b += kSortThreads) hist[b] = 0;
     __syncthreads();
-    for (int i = lo + t; i < hi; i += kBinThreads) atomicAdd(&hist[seg_bin[i]], 1);
+    uint32_t place[kSortItems];           // bin, and rank in it
+    if (in_lds) {
+#pragma unroll
+        for (int q = 0; q < kSortItems; ++q)
+            if (q * kSortThreads + t < n) {
+                const int b = share_bin(L, xy[q].x, xy[q].y, zu[q].x, first, nb);
+                place[q] = ((uint32_t)b << 16) | (uint32_t)atomicAdd(&hist[b], 1);
+            }
+    } else {
+        for (int i = lo + t; i < lo + n; i += kSortThreads)
+            atomicAdd(&hist[share_bin(L, staged[i].x, staged[i].y, staged[i].z, first, nb)], 1);
+    }
     __syncthreads();
     // exclusive scan of the bin counts: lane t takes bins [t*per, (t+1)*per)
-    const int per = (nb + kBinThreads - 1) / kBinThreads;
+    const int per = (nb + kSortThreads - 1) / kSortThreads;
     const int b0 = t * per;
     int s = 0;
     for (int q = 0; q < per; ++q)
         if (b0 + q < nb) s += hist[b0 + q];
     int tot;
-    int run = lo + block_scan_excl(s, &tot, lds);
-    int32_t* bo = bin_off + (int64_t)e * bl.per_event + bl.base[l];
+    int run = block_scan_excl(s, &tot, lds);
+    int32_t* bo = bin_off + (int64_t)e * bl.per_event + bl.base[l] + first;
     for (int q = 0; q < per; ++q)
         if (b0 + q < nb) {
             const int c = hist[b0 + q];
             hist[b0 + q] = run;
-            bo[b0 + q] = run;
+            bo[b0 + q] = lo + run;
             run += c;
         }
-    if (seg == n_seg - 1 && t == 0) bin_off[(int64_t)(e + 1) * bl.per_event] = hi;
+    // the event's last bin ends at an entry of its own
+    if (l == n_layers - 1 && share == split - 1 && t == 0) bo[nb] = lo + n;
     __syncthreads();
-    if (hi - lo <= kBinSrcCap) {
-        for (int i = lo + t; i < hi; i += kBinThreads) src[atomicAdd(&hist[seg_bin[i]], 1) - lo] = i;
+    if (in_lds) {
+#pragma unroll
+        for (int q = 0; q < kSortItems; ++q)
+            if (q * kSortThreads + t < n) {
+                float2* p = (float2*)&rec[hist[place[q] >> 16] + (int)(place[q] & 0xFFFFu)];
+                p[0] = xy[q];
+                p[1] = zu[q];
+                p[2] = vi[q];
+            }
         __syncthreads();
-        for (int j = t; j < hi - lo; j += kBinThreads) out[lo + j] = seg_rec[src[j]];
+        for (int j = t; j < n; j += kSortThreads) out[lo + j] = binned_record(rec[j]);
     } else {
-        for (int i = lo + t; i < hi; i += kBinThreads) out[atomicAdd(&hist[seg_bin[i]], 1)] = seg_rec[i];
+        // more hits than the LDS holds: straight to their places
+        for (int i = lo + t; i < lo + n; i += kSortThreads) {
+            const StagedHit h = staged[i];
+            out[lo + atomicAdd(&hist[share_bin(L, h.x, h.y, h.z, first, nb)], 1)] = binned_record(h);
+        }
     }
 }
 
@@ -860,7 +1172,7 @@ __device__ __attribute__((noinline)) LongList long_scan(LdsPtr<C> w, const Binne
             const int j = r * wlanes + ln;
             if (j < nseg) {
                 const int bb = u_lo + rr0 + j;
-                const int rb = row0 + (((bb % np) + np) % np) * n2;
+                const uint32_t rb = (uint32_t)row0 + (uint32_t)((((bb % np) + np) % np) * n2);
                 const int h0 = bin_off[rb + u_v0];
                 const int h1 = bin_off[rb + u_v1 + 1];
                 h0s[j] = h0;
@@ -1244,7 +1556,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
                     row_lo = b_lo;
                     v0 = coord_bin_of(float(Wn.vlo), float(L.lo), float(L.hi), n2);
                     v1 = coord_bin_of(float(Wn.vhi), float(L.lo), float(L.hi), n2);
-                    row0 = ev * a.bl.per_event + L.base;
+                    row0 = (int)((uint32_t)ev * (uint32_t)a.bl.per_event + (uint32_t)L.base);
                     const T rho = Tr<T>::sqrt_(p[0] * p[0] + p[1] * p[1]);
                     w.orec[ln64 * 8 + 3] = float(p[0] / rho);
                     w.orec[ln64 * 8 + 4] = float(p[1] / rho);
@@ -1365,7 +1677,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
                             const int bb = rw_par[64 + o] + (g - rw_par[o]);
                             const int vv = rw_par[128 + o], pp = rw_par[256 + o];
                             const int onp = pp & 0xFFFF, on2 = pp >> 16;
-                            const int rb = rw_par[192 + o] + (((bb % onp) + onp) % onp) * on2;
+                            const uint32_t rb = (uint32_t)rw_par[192 + o] + (uint32_t)((((bb % onp) + onp) % onp) * on2);
                             const int h0 = a.bin_off[rb + (vv & 0xFFFF)];
                             const int h1 = a.bin_off[rb + (vv >> 16) + 1];
                             sg_own[j] = o;
@@ -1815,36 +2127,71 @@ hipError_t launch_scan(const int32_t* in, int32_t* out, int64_t n, int32_t* bsum
     return hipGetLastError();
 }
 
+// Shares of a layer's phi rows that level 2 sorts by themselves: on average
+// half of what a workgroup's LDS holds (events differ), as long as a level-1
+// workgroup can count all of an event's.
+static int bin_split(int64_t n_hits, int n_events, int n_layers)
+{
+    const int64_t segs = (int64_t)n_events * (n_layers > 0 ? n_layers : 1);
+    int64_t k = (n_hits + segs * (kSortCap / 2) - 1) / (segs * (kSortCap / 2));
+    const int64_t most = kSegLocal / 2 / (n_layers > 0 ? n_layers : 1);
+    k = k < most ? k : most;
+    return (int)(k < 1 ? 1 : k);
+}
+
 hipError_t launch_bin(const FindPlan& pl, const kf_hits* h, const int32_t* event_off, int n_events,
-                      const kf_layer* d_layers, int n_layers, hipStream_t s)
+                      const kf_layer* layers, const kf_layer* d_layers, int n_layers, hipStream_t s)
 {
     hipError_t e;
-    const int64_t n_seg = (int64_t)n_events * n_layers;
-    if ((e = launch_fill(pl.seg_cnt, 2 * (n_seg + 1), 0, s)) != hipSuccess) return e;   // cnt and fill
-    const unsigned nchunk = blocks_for(h->n, kSegChunk);
-    if (h->n > 0) {
-        seg_count_kernel<<<nchunk, 256, 0, s>>>(h->n, h->layer, event_off, n_events, n_layers,
-                                                pl.hit_key, pl.seg_cnt);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+    const HitView v{h->x, h->y, h->z, h->su, h->sv, h->layer};
+    if (bin_direct(h->n, n_events)) {
+        int nb_max = 1;
+        for (int l = 0; l < n_layers; ++l) {
+            const int nb = layers[l].nbin_phi * layers[l].nbin_2;
+            nb_max = nb > nb_max ? nb : nb_max;
+        }
+        // shares of a layer of kDirectShare hits on average: a workgroup's
+        // gathers, a line a clock, are what the call waits for
+        const int64_t segs = (int64_t)n_events * n_layers;
+        int split = (int)(h->n / (segs * kDirectShare));
+        split = split < 1 ? 1 : (split < kDirectSplit ? split : kDirectSplit);
+        const size_t lds = sizeof(int) * ((size_t)nb_max + kBinCap);
+        // an event's workgroups run on kQueues / stride of the XCDs: four for a
+        // single event (56,000 hits: 27 us; 32 on two, 58 on one, where they
+        // stream at once); a grid takes fewer than 2^32 threads
+        int stride = n_events > 2 ? kQueues : 2 * n_events;
+        int64_t grid = (int64_t)((n_events + stride - 1) / stride) * stride * n_layers * split;
+        if (grid * kBinThreads > 0xffffffffLL) {
+            stride = 1;
+            grid = segs * split;
+        }
+        bin_kernel<<<(unsigned)grid, kBinThreads, lds, s>>>(v, h->n, event_off, n_events, stride, split, d_layers,
+                                                            n_layers, nb_max, pl.bl, pl.hit_key,
+                                                            pl.hit_bin, pl.hit_perm, pl.off,
+                                                            (BinnedHit*)pl.binned);
+        return hipGetLastError();
     }
-    if ((e = launch_scan(pl.seg_cnt, pl.seg_off, n_seg + 1, pl.bsum, s)) != hipSuccess) return e;
-    if (h->n > 0) {
-        seg_scatter_kernel<<<nchunk, 256, 0, s>>>(h->n, h->x, h->y, h->z, h->su, h->sv, event_off,
-                                                  n_events, d_layers, n_layers, pl.hit_key,
-                                                  pl.seg_off, pl.seg_fill, (BinnedHit*)pl.seg_rec,
-                                                  pl.seg_bin);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    // the largest layer's bin count, from the layout's per-layer bases
+    const int split = bin_split(h->n, n_events, n_layers);
+    const int64_t n_seg = (int64_t)n_events * n_layers * split;
     int nb_max = 1;
     for (int l = 0; l < n_layers; ++l) {
-        const int nb = (l + 1 < n_layers ? pl.bl.base[l + 1] : pl.bl.per_event) - pl.bl.base[l];
-        if (nb > nb_max) nb_max = nb;
+        const int nb = share_row(1, layers[l].nbin_phi, split) * layers[l].nbin_2;   // the first share's: the most
+        nb_max = nb > nb_max ? nb : nb_max;
     }
-    const size_t lds = sizeof(int) * ((size_t)nb_max + kBinSrcCap);
-    bin_segment_kernel<<<(unsigned)n_seg, kBinThreads, lds, s>>>(
-        pl.seg_off, (const BinnedHit*)pl.seg_rec, pl.seg_bin, d_layers, n_layers, (int)n_seg, nb_max,
-        pl.bl, pl.off, (BinnedHit*)pl.binned);
+    if ((e = launch_fill(pl.seg_cnt, n_seg + 1, 0, s)) != hipSuccess) return e;
+    const unsigned nchunk = blocks_for(h->n, kSegChunk);
+    seg_count_kernel<<<nchunk, 256, 0, s>>>(h->n, v, event_off, n_events, d_layers, n_layers, split,
+                                            pl.hit_key, pl.seg_cnt);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = launch_scan(pl.seg_cnt, pl.seg_off, n_seg + 1, pl.bsum, s)) != hipSuccess) return e;
+    // (seg_cnt then counts down the places left in every segment)
+    seg_scatter_kernel<<<nchunk, kSegThreads, 0, s>>>(h->n, v, event_off, n_events, n_layers * split,
+                                                      pl.hit_key, pl.seg_off, pl.seg_cnt,
+                                                      (StagedHit*)pl.staged);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    bin_segment_kernel<<<(unsigned)n_seg, kSortThreads, sizeof(int) * (size_t)nb_max, s>>>(
+        pl.seg_off, (const StagedHit*)pl.staged, d_layers, n_layers, split, pl.bl, pl.off,
+        (BinnedHit*)pl.binned);
     return hipGetLastError();
 }
 
@@ -2188,21 +2535,25 @@ size_t plan_find(FindPlan* pl, void* base, int64_t n_hits, int n_events, int64_t
         off += (bytes + 255) & ~size_t(255);
         return p;
     };
-    const int64_t nb = (int64_t)n_events * pl->bl.per_event + 1;
+    const int64_t nb = (int64_t)n_events * pl->bl.per_event;
     const int64_t nc = (int64_t)n_events * kSeedCells + 1;
     const int64_t ns = n_seeds > 0 ? n_seeds : 1;
     const int64_t nh = n_hits > 0 ? n_hits : 1;
-    const int64_t nseg = (int64_t)n_events * n_layers + 1;
+    const bool direct = bin_direct(n_hits, n_events);
+    const int64_t nseg = direct ? 0 : (int64_t)n_events * n_layers * bin_split(n_hits, n_events, n_layers) + 1;
     int64_t nsmax = nseg > nc ? nseg : nc;
     if (nh + 1 > nsmax) nsmax = nh + 1;
     const int64_t nsum = (nsmax + kScanChunk - 1) / kScanChunk;
-    pl->seg_cnt = (int32_t*)take(sizeof(int32_t) * 2 * nseg);
-    pl->seg_fill = pl->seg_cnt + nseg;
-    pl->seg_off = (int32_t*)take(sizeof(int32_t) * nseg);
     pl->off = (int32_t*)take(sizeof(int32_t) * nb);
     pl->hit_key = (int32_t*)take(sizeof(int32_t) * nh);
-    pl->seg_rec = take(sizeof(BinnedHit) * nh);
-    pl->seg_bin = (int32_t*)take(sizeof(int32_t) * nh);
+    if (direct) {
+        pl->hit_bin = (int32_t*)take(sizeof(int32_t) * nh);
+        pl->hit_perm = (int32_t*)take(sizeof(int32_t) * nh);
+    } else {
+        pl->seg_cnt = (int32_t*)take(sizeof(int32_t) * nseg);
+        pl->seg_off = (int32_t*)take(sizeof(int32_t) * nseg);
+        pl->staged = take(sizeof(StagedHit) * nh);
+    }
     pl->binned = take(sizeof(BinnedHit) * nh);
     pl->scnt = (int32_t*)take(sizeof(int32_t) * nc);
     pl->soff = (int32_t*)take(sizeof(int32_t) * nc);

@@ -23,7 +23,8 @@ struct alignas(16) BinnedHit {
 };
 
 // Bin layout of one event: layer l owns bins [base[l], base[l] + nbin_phi*nbin_2),
-// phi-major; events are per_event bins apart.
+// phi-major; an entry for the end of the last bin follows, and events are
+// per_event entries apart (32 bits hold an entry's number without sign).
 struct BinLayout {
     int32_t base[kMaxLayers];
     int32_t per_event;
@@ -86,13 +87,16 @@ struct CleanRec {
 
 struct FindPlan {
     BinLayout bl;
-    int32_t* seg_cnt;   // [n_events * n_layers + 1] hits per (event, layer) segment
-    int32_t* seg_fill;  // [n_events * n_layers + 1] hits placed per segment so far
-    int32_t* seg_off;   // [n_events * n_layers + 1] exclusive prefix sum of seg_cnt
-    int32_t* off;       // [n_events * per_event + 1] first binned hit of every bin
-    int32_t* hit_key;   // [n_hits] segment of each hit (-1: not binned)
-    void* seg_rec;      // [n_hits] hit records grouped by segment (32 bytes each)
-    int32_t* seg_bin;   // [n_hits] bin of each grouped record within its layer
+    int32_t* off;       // [n_events * per_event] first binned hit of every bin
+    // two-level binning, [n_hits] or [segments + 1] (a share of a layer's phi rows in one event)
+    int32_t* hit_key;   // segment of each hit (-1: not binned)
+    int32_t* seg_cnt;   // hits per segment, then places left in it
+    int32_t* seg_off;   // exclusive prefix sum of seg_cnt
+    void* staged;       // the hits grouped by segment (24 bytes each)
+    // direct binning, where a layer of an event has more hits than the LDS holds:
+    // the hits (hit_key), their bins, and the hits in bin order
+    int32_t* hit_bin;
+    int32_t* hit_perm;
     void* binned;       // [n_hits] records of 32 bytes
     int32_t* scnt;      // [n_events * cells + 1] seeds per (event, eta, phi) cell
     int32_t* soff;      // [n_events * cells + 1] its exclusive prefix sum
@@ -123,7 +127,7 @@ hipError_t find_max_blocks_per_cu(int W, int nl, int prec, bool learn, bool mat,
 hipError_t launch_scan(const int32_t* in, int32_t* out, int64_t n, int32_t* bsum, hipStream_t s);
 hipError_t launch_fill(int32_t* p, int64_t n, int32_t v, hipStream_t s);
 hipError_t launch_bin(const FindPlan& pl, const kf_hits* h, const int32_t* event_off, int n_events,
-                      const kf_layer* d_layers, int n_layers, hipStream_t s);
+                      const kf_layer* layers, const kf_layer* d_layers, int n_layers, hipStream_t s);
 // Seed cleaning over the cells the seed order just built (pl.cell, pl.soff,
 // pl.order): marks or clears KF_ST_DUPLICATE in seeds->status.
 hipError_t launch_clean(const FindPlan& pl, const kf_tracks* seeds, const int32_t* seed_event,
