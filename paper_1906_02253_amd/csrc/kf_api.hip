@@ -257,13 +257,16 @@ hipError_t phase_bin(const kf_ctx* ctx, const kfmi::FindLaunch& L, hipStream_t s
 
 hipError_t phase_order(const kf_ctx* ctx, const kfmi::FindLaunch& L, hipStream_t s)
 {
+    // (the seed cleaning reads the cells)
+    if (!L.clean && kfmi::small_order(L.seeds->n, (int)L.n_events))
+        return kfmi::launch_small_order(L.pl, L.seeds, L.seed_event, L.event_off, (int)L.n_events,
+                                        L.largest_first, L.a.n_tiles, L.a.seeds_per_tile, s);
     hipError_t e = kfmi::launch_seed_order(L.pl, L.seeds, L.seed_event, L.event_off,
                                            (int)L.n_events, L.largest_first, s);
     if (e == hipSuccess && L.clean)
         e = kfmi::launch_clean(L.pl, L.seeds, L.seed_event, (int)L.n_events, L.seed_hits,
                                L.hits->n, ctx->params, s);
     if (e == hipSuccess) e = kfmi::launch_cost_order(L.pl, L.seeds, L.a.n_tiles, L.a.seeds_per_tile, s);
-    if (e == hipSuccess) e = kfmi::launch_fill(L.pl.tile_counter, kfmi::kQueues * kfmi::kQueueStride, 0, s);
     return e;
 }
 

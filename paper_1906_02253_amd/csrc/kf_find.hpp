@@ -98,7 +98,8 @@ struct FindPlan {
     int32_t* hit_bin;
     int32_t* hit_perm;
     void* binned;       // [n_hits] records of 32 bytes
-    int32_t* scnt;      // [n_events * cells + 1] seeds per (event, eta, phi) cell
+    int32_t* scnt;      // [n_events * cells + 1] seeds per (event, eta, phi) cell, zero
+                        // again once they are placed
     int32_t* soff;      // [n_events * cells + 1] its exclusive prefix sum
     int32_t* erank;     // [n_events] processing position of each event
     int32_t* cell;      // [n_seeds] cell of each seed
@@ -109,7 +110,7 @@ struct FindPlan {
     int32_t* queue_loopers;  // [kQueues] seeds of the costliest class in each queue's range
     int32_t* bsum;      // chunk totals of the prefix sums
     int2* bp;
-    int32_t* tile_counter;
+    int32_t* tile_counter;  // [kQueues * kQueueStride]
     unsigned long long* clean_best;  // [n_hits] best seed claiming each hit (seed cleaning)
     CleanRec* clean_rec;      // [n_seeds] cleaning records in seed (cell) order
     int32_t* dup_cnt;         // [n_hits + 1] tracks per hit (duplicate removal)
@@ -137,6 +138,12 @@ hipError_t launch_clean(const FindPlan& pl, const kf_tracks* seeds, const int32_
 hipError_t launch_dedup(const FindPlan& pl, int64_t n, int nl, const int32_t* rows,
                         const float* chi2, uint32_t* status, const int32_t* event, int64_t n_hits,
                         double frac, hipStream_t s);
+// The finding kernel's tile order (pl.tile_order) of a few seeds in one launch;
+// clears the tile counters.
+bool small_order(int64_t n_seeds, int n_events);
+hipError_t launch_small_order(const FindPlan& pl, const kf_tracks* seeds, const int32_t* seed_event,
+                              const int32_t* event_off, int n_events, int largest_first, int n_tiles,
+                              int seeds_per_tile, hipStream_t s);
 // The finding kernel's tile order (pl.tile_order) from the cell order.
 hipError_t launch_cost_order(const FindPlan& pl, const kf_tracks* seeds, int n_tiles,
                              int seeds_per_tile, hipStream_t s);
