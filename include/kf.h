@@ -311,7 +311,7 @@ int kf_find(kf_ctx* ctx, const kf_hits* hits, const int32_t* event_off, int32_t 
  * runs on until the process ends (its address looked up once per device by
  * kf_create), instead of the context's workspace.  No allocation, no
  * freeing, no phase timing.  A call whose scratch would exceed 64 MiB
- * (about 88 B per hit, 140 B per seed, the back-pointers of the resident
+ * (about 76 B per hit, 140 B per seed, the back-pointers of the resident
  * workgroups and 0.4 MB of bins per event at 24 layers of 128 x 32 bins)
  * returns KF_EINVAL with the sizes in kf_last_error.  Every call on one
  * device shares that device's array and leaves its contents behind (each

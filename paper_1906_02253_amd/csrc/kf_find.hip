@@ -4,7 +4,7 @@
 //       into 32-byte records (paper Sec. 3.2: hits handed in by the caller;
 //       binning makes the per-layer hit search a contiguous range scan);
 //   a2  order seeds by (event, eta bin, phi bin), events optionally largest
-//       first, with a counting sort, so that a workgroup's seeds share hit
+//       first, so that a wave's seeds share hit
 //       bins (paper Sec. 3.2: seeds grouped close in eta and phi for cache
 //       reuse of hit data);
 //   a3-a7 one persistent kernel walks tiles of seeds through the detector
@@ -12,10 +12,9 @@
 //       layer propagation; Sec. 4: hit-search windows, candidate scoring):
 //       each lane owns one candidate slot (max_cands slots per seed), keeps
 //       its state in registers, propagates to its next surface, scans the
-//       window's bins for hits passing the chi2 cut, then the seed's slot-0
-//       lane merges the children of all its candidates (k-way merge of
-//       per-parent sorted lists) and the lanes materialise the survivors with
-//       the Kalman update.  Hit lists are recovered from per-step
+//       window's bins for hits passing the chi2 cut, then the seed's lanes
+//       rank the children of all its candidates side by side and materialise
+//       the survivors with the Kalman update.  Hit lists are recovered from per-step
 //       back-pointers at the end.
 #include "kf_find.hpp"
 #include "kf_math.hpp"
