@@ -1121,30 +1121,6 @@ __device__ inline bool chi2_test(const float4& oa, const float4& ob, const C pc[
     return c2u < U(cut);
 }
 
-// Whether the hit's chi2 can be below `below` (in FP32, to be on the safe
-// side): chi2 >= ru^2 / S00 and >= rv^2 / S11 for any covariance, each residual
-// taken smaller and each variance larger than its rounding can make it.
-__device__ inline bool chi2_may_be_below(const float4& oa, const float4& ob, const float pf[6], const float4& r0,
-                                         const float4& r1, float below)
-{
-    const float c = r1.y, s = r1.z, dx = r0.x - oa.x, dy = r0.y - oa.y;
-    const float slack = 1e-6f * (fabsf(dx) + fabsf(dy));
-    const float pt = 4e-6f * (pf[0] + pf[3]);
-    const float ru = fmaxf(fabsf(c * dy - s * dx) - slack, 0.0f);
-    const float s00 = s * s * pf[0] - 2.0f * s * c * pf[1] + c * c * pf[3] + r0.w * r0.w + pt;
-    float rv, s11;
-    if ((__float_as_int(ob.w) >> 1) == 0) {
-        rv = fabsf(r0.z - oa.z);
-        s11 = pf[5] + r1.x * r1.x;
-    } else {
-        rv = fmaxf(fabsf(c * dx + s * dy) - slack, 0.0f);
-        s11 = c * c * pf[0] + 2.0f * s * c * pf[1] + s * s * pf[3] + r1.x * r1.x + pt;
-    }
-    const float lim = 1.0001f * below;
-    // (a comparison with NaN leaves it to the exact test)
-    return !(ru * ru > lim * s00) && !(rv * rv > lim * s11);
-}
-
 constexpr int kSeg = 128;       // phi rows queued per wave per round
 constexpr int kScanBatch = 4;   // hits per lane in flight in the scan
 constexpr int kAcc = 64 * kScanBatch;
@@ -1249,8 +1225,7 @@ __device__ inline int row_prefix(LEN len, PRE pre, int nseg, int wlanes)
 struct LongList {
     uint64_t best;      // lane 8 k + q: entry q of the k-th window
     int bi;             // its binned index
-    int count;          // lanes 8 k ..: hits below the cut in the k-th window (all of them until
-                        // there are MC)
+    int count;          // lanes 8 k ..: hits below the cut in the k-th window
     unsigned tests;     // chi2 tests of this lane
 };
 
@@ -1327,23 +1302,13 @@ __device__ __attribute__((noinline)) LongList long_scan(LdsPtr<C> w, const Binne
                 for (int q = 0; q < 6; ++q) pc[q] = w->ocov[l * kOwnCov<C> + q];
                 const float4 oa = make_float4(rec[0], rec[1], rec[2], rec[3]);
                 const float4 ob = make_float4(rec[4], rec[5], rec[6], rec[7]);
-                float pf[6];
-#pragma unroll
-                for (int q = 0; q < 6; ++q) pf[q] = float(pc[q]);
                 const bool mine = ln >> 3 == k;
                 uint64_t kth = readlane64(L.best, 8 * k + MC - 1);
 #pragma unroll
                 for (int q = 0; q < kScanBatch; ++q) {
-                    // the exact chi2 only of hits that may enter the list; the others
-                    // matter no more once it is full (count says whether it is)
                     float c2f = 0.0f;
-                    const bool in = bix[q] >= 0 && window_test<T>(oa, ob, r0[q], r1[q]);
-                    L.tests += in ? 1 : 0;
-                    const float below = kth == ~0ull ? __uint_as_float(0x7f800000u) : fmaxf(child_key_chi2(kth), 1e-3f);
-                    bool ok = in && chi2_may_be_below(oa, ob, pf, r0[q], r1[q], below);
-                    if (__ballot(ok) == 0) continue;
-                    unsigned counted = 0;
-                    if (ok) ok = chi2_test<T, C, U>(oa, ob, pc, r0[q], r1[q], cut, &counted, &c2f);
+                    bool ok = bix[q] >= 0 && window_test<T>(oa, ob, r0[q], r1[q]);
+                    if (ok) ok = chi2_test<T, C, U>(oa, ob, pc, r0[q], r1[q], cut, &L.tests, &c2f);
                     const int n_ok = __popcll(__ballot(ok));
                     L.count += mine ? n_ok : 0;
                     uint64_t e = ok ? child_key(c2f, __float_as_int(r1[q].w)) : ~0ull;
