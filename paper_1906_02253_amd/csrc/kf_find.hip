@@ -1170,6 +1170,7 @@ struct alignas(16) WaveLds {
             int32_t cbidx[kMaxCands * 64];   // binned index of each candidate's accepted hits
         };
     };
+    int32_t finite;             // whether the tile's seeds have finite covariances (see transport)
 };
 
 // LDS of a workgroup: the layers, the navigation's surface orders, then each
@@ -1472,7 +1473,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
             for (int k = 0; k < 6; ++k) p[k] = T(a.spar[k * a.sld + sid]);
 #pragma unroll
             for (int k = 0; k < 21; ++k) P[k] = C(scov[k * a.sld + sid]);
-            poison_nonfinite(P);
             chi2 = a.schi2[sid];
             nhits = (a.sndf[sid] + 5) / 2;
             status = a.sstatus[sid] | (bad_event ? (uint32_t)KF_ST_BADINPUT : 0u);
@@ -1483,6 +1483,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
 #pragma unroll
             for (int k = 0; k < 21; ++k) P[k] = C(0);
         }
+        if (ln64 == 0) w.finite = 1;
+        wave_fence();
+        if (!all_finite(P)) w.finite = 0;
+        wave_fence();
         // steering: the seed's region and the plan entry after its last seed
         // layer (every lane of the seed computes the same)
         int rg = 0, pos = 0;
@@ -1560,9 +1564,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
                     ++n_prop;
                     const FindLayer L = layers[layer];
                     if constexpr (FIELD)
-                        field_transport(p, P, fq, fl, a.prm, L.kind, T(L.r_or_z));
+                        field_transport(p, P, fq, fl, a.prm, L.kind, T(L.r_or_z),
+                                        w.finite != 0);
                     else
-                        transport(p, P, s, kb, L.kind, T(L.r_or_z), sth, cth);
+                        transport(p, P, s, kb, L.kind, T(L.r_or_z), sth, cth,
+                                  w.finite != 0);
                     if (a.material) {
                         if constexpr (MAT)
                             add_material(p, P, L, a.mat, T(a.prm.mass));

@@ -34,7 +34,6 @@ __device__ inline void load_state(const T* par, const T* cov, int64_t ld, int64_
     q = cov + b0;
 #pragma unroll
     for (int k = 0; k < 21; ++k, q += row) P[k] = C(q[i]);
-    poison_nonfinite(P);
 }
 
 template <typename T, typename C, typename U>
@@ -74,11 +73,11 @@ __device__ inline void stage_layers(const kf_layer* layers, int n_layers, StepLa
 // start (counted in *fallbacks).
 // FIELD: the parametrised field (kf_params.field_z0 > 0); MAT: the r-z material
 // map.  Both are compile-time variants so that the uniform-field, per-layer
-// material instantiation keeps its register budget.
+// material instantiation keeps its register budget.  finite: see transport.
 template <typename T, typename C, typename U, bool FIELD, bool MAT>
 __device__ inline int propagate_to(U p[6], C P[21], const StepLayer<T>& L, const kf_params& prm,
-                                   bool material, const MatMap& mat, T s_init, T* s_out, int* evals,
-                                   int* fallbacks)
+                                   bool material, const MatMap& mat, bool finite, T s_init, T* s_out,
+                                   int* evals, int* fallbacks)
 {
     const T kb = T(kKappa) * T(prm.bz);
     T pt[6];
@@ -103,7 +102,7 @@ __device__ inline int propagate_to(U p[6], C P[21], const StepLayer<T>& L, const
                                     prm.mlp_max_iter, &l, q, evals, fallbacks);
         }
         if (st) return st;
-        field_transport(p, P, q, l, prm, L.kind, T(L.r_or_z));
+        field_transport(p, P, q, l, prm, L.kind, T(L.r_or_z), finite);
         if (material) {
             if constexpr (MAT)
                 add_material(p, P, L, mat, T(prm.mass));
@@ -131,7 +130,7 @@ __device__ inline int propagate_to(U p[6], C P[21], const StepLayer<T>& L, const
         *evals += 1;
         if (s < T(0)) return KF_ST_UNREACHABLE;
     }
-    transport(p, P, s, kb, L.kind, T(L.r_or_z), st_, ct_);
+    transport(p, P, s, kb, L.kind, T(L.r_or_z), st_, ct_, finite);
     if (material) {
         if constexpr (MAT)
             add_material(p, P, L, mat, T(prm.mass));
@@ -259,7 +258,8 @@ __global__ __launch_bounds__(256) void propagate_kernel(int64_t n, int64_t ld, T
     }
     T s = T(0);
     int ev = 0, fb = 0;
-    int r = propagate_to<T, C, U, FIELD, MAT>(p, P, L, prm, material != 0, mat, s_init, &s, &ev, &fb);
+    const bool finite = wave_all(all_finite(P));
+    int r = propagate_to<T, C, U, FIELD, MAT>(p, P, L, prm, material != 0, mat, finite, s_init, &s, &ev, &fb);
     if (fb) st |= KF_ST_FALLBACK;
     if (r) {
         st |= (uint32_t)r;
@@ -350,6 +350,7 @@ __global__ __launch_bounds__(256, 2) void fit_kernel(FitArgs a, int k0, int k1, 
     U p[6];
     C P[21];
     if (alive) load_state(par, cov, ld, b0, i, p, P);
+    const bool finite = wave_all(!alive || all_finite(P));
     FitHit hit = load_hit(now);
     bool touched = false;
     for (int k = k0; k < k1; ++k) {
@@ -385,8 +386,8 @@ __global__ __launch_bounds__(256, 2) void fit_kernel(FitArgs a, int k0, int k1, 
         }
         if (!alive) continue;
         int ev = 0, fb = 0;
-        int r = propagate_to<T, C, U, FIELD, MAT>(p, P, L, a.prm, a.material != 0, a.mat, s_init,
-                                                   (T*)nullptr, &ev, &fb);
+        int r = propagate_to<T, C, U, FIELD, MAT>(p, P, L, a.prm, a.material != 0, a.mat, finite,
+                                                   s_init, (T*)nullptr, &ev, &fb);
         touched = true;
         if (fb) st |= KF_ST_FALLBACK;
         if (r) {

@@ -298,22 +298,17 @@ KF_HD inline void sandwich(const T F[4][6], C P[21])
     sched_fence();
 }
 
-// A covariance with an entry that is not finite becomes NaN throughout, as the
-// full product F P F^T makes it, so that leaving out zeros hides nothing.
+// Whether every entry of a covariance is finite.
 template <typename C>
-KF_HD inline void poison_nonfinite(C P[21])
+KF_HD inline bool all_finite(const C P[21])
 {
     C z = C(0);
 #pragma unroll
     for (int k = 0; k < 21; ++k) z += C(0) * P[k];
-    if (!(z == C(0))) {
-#pragma unroll
-        for (int k = 0; k < 21; ++k) P[k] = z;
-    }
+    return z == C(0);
 }
 
-// Whether every active lane of the wave is on a surface of this kind (host
-// code: whether this one is).
+// Whether c holds in every active lane of the wave (host code: here).
 KF_HD inline bool wave_all(bool c)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -330,8 +325,11 @@ KF_HD inline bool wave_all(bool c)
 // computed in T and added in S, so the predicted state carries no rounding
 // to T before the update that consumes it); F P F^T is accumulated in C.
 // st, ct: sine and cosine of theta, which the transport leaves as it is.
+// finite (the same in the whole wave): every covariance of the wave was finite
+// when it was loaded.  A zero of F times an infinity or a NaN is no zero, so a
+// wave with such a covariance takes the full product.
 template <typename T, typename C, typename S>
-KF_HD inline void transport(S p[6], C P[21], T s, T kb, int kind, T zd, T st, T ct)
+KF_HD inline void transport(S p[6], C P[21], T s, T kb, int kind, T zd, T st, T ct, bool finite)
 {
     const T x = T(p[0]), y = T(p[1]), z = T(p[2]), c = T(p[3]), phi = T(p[4]);
     const T h = -kb * c;
@@ -367,8 +365,8 @@ KF_HD inline void transport(S p[6], C P[21], T s, T kb, int kind, T zd, T st, T 
         {f2 * d0, f2 * d1, T(1) + f2 * d2, f2 * d3, f2 * d4, D25 + f2 * d5},
         {f4 * d0, f4 * d1, f4 * d2, D43 + f4 * d3, T(1) + f4 * d4, f4 * d5},
     };
-    // the sparse product where the whole wave is on one kind of surface
-    if (wave_all(kind == 0))
+    // the sparse product where the whole wave is on barrels
+    if (finite && wave_all(kind == 0))
         sandwich<0>(F, P);
     else
         sandwich<-1>(F, P);
@@ -379,11 +377,11 @@ KF_HD inline void transport(S p[6], C P[21], T s, T kb, int kind, T zd, T st, T 
 }
 
 template <typename T, typename C, typename S>
-KF_HD inline void transport(S p[6], C P[21], T s, T kb, int kind, T zd)
+KF_HD inline void transport(S p[6], C P[21], T s, T kb, int kind, T zd, bool finite = true)
 {
     T st, ct;
     Tr<T>::sincos_(T(p[5]), &st, &ct);
-    transport(p, P, s, kb, kind, zd, st, ct);
+    transport(p, P, s, kb, kind, zd, st, ct, finite);
 }
 
 // Multiple-scattering process noise of a layer (PDG Highland width), added to
@@ -788,7 +786,7 @@ KF_HD inline T effective_bz(T B0, T Z0, T x, T y, T z, T phi, T theta)
 
 template <typename T, typename C, typename S>
 KF_HD inline void field_transport(S p[6], C P[21], const T q[6], T l, const kf_params& prm, int kind,
-                                  T zd)
+                                  T zd, bool finite = true)
 {
     T pc[6];
 #pragma unroll
@@ -801,7 +799,7 @@ KF_HD inline void field_transport(S p[6], C P[21], const T q[6], T l, const kf_p
                                half * (pc[5] + q[5]));
     const T b_b = effective_bz(B0, Z0, q[0], q[1], q[2], q[4], q[5]);
     const T kb = T(kKappa) * ((b_a + T(4) * b_m + b_b) / T(6));
-    transport(pc, P, l * Tr<T>::sin_(pc[5]), kb, kind, zd);
+    transport(pc, P, l * Tr<T>::sin_(pc[5]), kb, kind, zd, finite);
 #pragma unroll
     for (int k = 0; k < 6; ++k) p[k] = S(q[k]);
     p[4] = wrap_phi(p[4]);
