@@ -138,6 +138,40 @@ __device__ inline BinnedHit binned_record(const HitView& h, int32_t i)
     return r;
 }
 
+// The hits [*lo, *hi) of n_hits that event e owns: those whose search
+// (event_of) ends at it, which is the interval between the offsets that the
+// search passes on the way, each loaded by a lane of its own.  With rising
+// offsets these are off[e] and off[e + 1]; where the offsets decrease or lie
+// outside the hits, every hit still has one event at most.  Called by whole
+// waves.
+__device__ inline void event_range(const int32_t* __restrict__ off, int n_events, int e, int32_t n_hits,
+                                   uint32_t* lo, uint32_t* hi)
+{
+    const int ln = threadIdx.x & 63;
+    int a = 0, b = n_events, mine = ln == 0 ? 0 : (ln == 1 ? n_events : -1);
+    bool left = ln == 0;                    // an offset at or below the event's hits
+    for (int step = 2; b - a > 1; ++step) {
+        const int mid = (a + b) >> 1;
+        if (ln == step) {
+            mine = mid;
+            left = e >= mid;
+        }
+        if (e >= mid) a = mid;
+        else b = mid;
+    }
+    int v = mine >= 0 ? off[mine] : 0;
+    v = v < 0 ? 0 : (v < n_hits ? v : n_hits);
+    int l = mine >= 0 && left ? v : 0, h = mine >= 0 && !left ? v : n_hits;
+    for (int o = 32; o > 0; o >>= 1) {
+        const int lo2 = __shfl_xor(l, o), hi2 = __shfl_xor(h, o);
+        l = lo2 > l ? lo2 : l;
+        h = hi2 < h ? hi2 : h;
+    }
+    *lo = (uint32_t)__builtin_amdgcn_readfirstlane(l);
+    h = __builtin_amdgcn_readfirstlane(h);
+    *hi = *lo > (uint32_t)h ? *lo : (uint32_t)h;
+}
+
 // Streams layer[lo, hi): f(number in the list, hit) for every hit of layer l,
 // in any order; *cnt (LDS, zero on entry) counts them.  Returns this lane's
 // hits of lower layers.
@@ -196,10 +230,8 @@ __global__ __launch_bounds__(kBinThreads) void bin_kernel(
     const kf_layer& L = layers[l];
     int first = share_row(share, L.nbin_phi, split) * L.nbin_2;
     int nb = share_row(share + 1, L.nbin_phi, split) * L.nbin_2 - first;
-    // (offsets outside the hits, or that decrease, leave an event without hits)
-    const int64_t o0 = event_off[e], o1 = event_off[e + 1];
-    const uint32_t lo = (uint32_t)(o0 < 0 ? 0 : (o0 < n_hits ? o0 : n_hits));
-    const uint32_t hi = (uint32_t)(o1 < (int64_t)lo ? (int64_t)lo : (o1 < n_hits ? o1 : n_hits));
+    uint32_t lo, hi;
+    event_range(event_off, n_events, e, (int32_t)n_hits, &lo, &hi);
     for (int b = t; b < nb_max; b += kBinThreads) hist[b] = 0;
     if (t < 2) cnt[t] = 0;
     __syncthreads();
