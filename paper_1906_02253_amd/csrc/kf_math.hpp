@@ -514,15 +514,8 @@ KF_HD inline HitFrame<U> hit_frame(float x, float y, float z, float su, float sv
     f.hy = U(y);
     f.hz = U(z);
     U rho = Tr<U>::sqrt_(f.hx * f.hx + f.hy * f.hy);
-    if constexpr (sizeof(U) == 8) {
-        // in 64 bits one division serves both (an ulp off a division each)
-        const U inv = U(1) / rho;
-        f.c = f.hx * inv;
-        f.s = f.hy * inv;
-    } else {
-        f.c = f.hx / rho;
-        f.s = f.hy / rho;
-    }
+    f.c = f.hx / rho;
+    f.s = f.hy / rho;
     f.vu = U(su) * U(su);
     f.vv = U(sv) * U(sv);
     return f;
