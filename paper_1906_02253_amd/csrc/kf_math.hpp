@@ -46,6 +46,7 @@ template <> struct Tr<float> {
     KF_HD static inline float sin_(float x) { return sinf(x); }
     KF_HD static inline float floor_(float x) { return floorf(x); }
     KF_HD static inline float min_(float a, float b) { return fminf(a, b); }
+    KF_HD static inline float fma_(float a, float b, float c) { return fmaf(a, b, c); }
 };
 template <> struct Tr<double> {
     KF_HD static inline void sincos_(double x, double* s, double* c) { sincos(x, s, c); }
@@ -59,6 +60,7 @@ template <> struct Tr<double> {
     KF_HD static inline double sin_(double x) { return sin(x); }
     KF_HD static inline double floor_(double x) { return floor(x); }
     KF_HD static inline double min_(double a, double b) { return fmin(a, b); }
+    KF_HD static inline double fma_(double a, double b, double c) { return fma(a, b, c); }
 };
 
 template <typename T>
@@ -584,7 +586,9 @@ KF_HD inline int kf_update_kind(T p[6], C P[21], const HitFrame<U>& f, int kind,
     if (!(det > U(0)) || !(S00 > U(0))) return KF_ST_NONPD;
     U idet = U(1) / det;
     U I00 = S11 * idet, I01 = -S01 * idet, I11 = S00 * idet;
-    *chi2_out = ru * (I00 * ru + I01 * rv) + rv * (I01 * ru + I11 * rv);
+    // (fused by hand: left to the compiler, the known kind and the other rounded
+    // differently, and a track's chi2 depended on the tracks of its wave)
+    *chi2_out = Tr<U>::fma_(ru, Tr<U>::fma_(I00, ru, I01 * rv), rv * Tr<U>::fma_(I01, ru, I11 * rv));
     U K0[6], K1[6];
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
