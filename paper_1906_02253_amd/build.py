@@ -7,7 +7,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libkfmi.so")
-SOURCES = ["kf_api.hip", "kf_fit.hip", "kf_find.hip", "kf_mlp.hip"]
+SOURCES = ["kf_api.hip", "kf_fit.hip", "kf_fit64.hip", "kf_find.hip", "kf_mlp.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",
@@ -22,6 +22,9 @@ HIPCC_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-fno-gpu-flush-denormals-to-zero",
 ]
+
+# flags of single sources (the reason stands in the source)
+SOURCE_FLAGS = {"kf_fit64.hip": ["-mllvm", "-disable-machine-licm"]}
 
 
 def hipcc():
@@ -64,7 +67,7 @@ def build(verbose=False, extra=()):
 
     def compile_one(so):
         src, obj = so
-        cmd = [hipcc(), *flags, *extra, "-c", "-o", obj, src]
+        cmd = [hipcc(), *flags, *SOURCE_FLAGS.get(os.path.basename(src), ()), *extra, "-c", "-o", obj, src]
         if verbose:
             print(" ".join(cmd), flush=True)
         return subprocess.run(cmd, capture_output=True, text=True)

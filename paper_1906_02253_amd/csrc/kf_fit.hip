@@ -4,145 +4,9 @@
 // arXiv:1906.02253 Sec. 2 (vectorised KF track fitting over sets of small
 // matrices), Sec. 3.1 (layer-to-layer propagation with per-layer material in
 // a constant field), Sec. 3.2 (seeds provided externally).
-#include "kf_internal.hpp"
-#include "kf_math.hpp"
-#include "kf_mlp.hpp"
+#include "kf_fit.hpp"
 
 namespace kfmi {
-
-// par and cov are stored in T, the state precision (FP32 in the mixed and
-// FP32 modes); in registers the state is held in U (the update precision) and
-// the covariance in C (the covariance-arithmetic precision).
-// A workgroup's elements start at b0 and lane i takes element b0 + i.  The row
-// stride is made opaque at each use, so that the compiler steps one scalar
-// address from row to row there instead of keeping all 27 rows' addresses in
-// 54 vector registers from the load to the store.
-__device__ inline int64_t opaque(int64_t v)
-{
-    asm volatile("" : "+s"(v));
-    return v;
-}
-
-template <typename T, typename C, typename U>
-__device__ inline void load_state(const T* par, const T* cov, int64_t ld, int64_t b0, unsigned i, U p[6],
-                                  C P[21])
-{
-    const int64_t row = opaque(ld);
-    const T* q = par + b0;
-#pragma unroll
-    for (int k = 0; k < 6; ++k, q += row) p[k] = U(q[i]);
-    q = cov + b0;
-#pragma unroll
-    for (int k = 0; k < 21; ++k, q += row) P[k] = C(q[i]);
-}
-
-template <typename T, typename C, typename U>
-__device__ inline void store_state(T* par, T* cov, int64_t ld, int64_t b0, unsigned i, const U p[6],
-                                   const C P[21])
-{
-    const int64_t row = opaque(ld);
-    T* q = par + b0;
-#pragma unroll
-    for (int k = 0; k < 6; ++k, q += row) q[i] = T(p[k]);
-    q = cov + b0;
-#pragma unroll
-    for (int k = 0; k < 21; ++k, q += row) q[i] = T(P[k]);
-}
-
-// A layer as propagate_to reads it.
-template <typename T>
-struct StepLayer {
-    int32_t kind;
-    T r_or_z, x0;
-};
-
-// The layers' StepLayers in LDS; every thread of the workgroup calls it.
-template <typename T>
-__device__ inline void stage_layers(const kf_layer* layers, int n_layers, StepLayer<T>* out)
-{
-    for (int l = threadIdx.x; l < n_layers; l += blockDim.x)
-        out[l] = StepLayer<T>{layers[l].kind, T(layers[l].r_or_z), T(layers[l].x0)};
-    __syncthreads();
-}
-
-// Propagate (p, P) to layer L.  The surface solve, the helix and the
-// transport Jacobian run in T on the state rounded to T; the state itself
-// stays in U (transport adds the T increments in U) and the covariance in C.
-// s_init < 0: straight-line start; otherwise the learned start with
-// prm.mlp_max_iter evaluations before the fallback to the straight-line
-// start (counted in *fallbacks).
-// FIELD: the parametrised field (kf_params.field_z0 > 0); MAT: the r-z material
-// map.  Both are compile-time variants so that the uniform-field, per-layer
-// material instantiation keeps its register budget.  finite: see transport.
-template <typename T, typename C, typename U, bool FIELD, bool MAT>
-__device__ inline int propagate_to(U p[6], C P[21], const StepLayer<T>& L, const kf_params& prm,
-                                   bool material, const MatMap& mat, bool finite, T s_init, T* s_out,
-                                   int* evals, int* fallbacks)
-{
-    const T kb = T(kKappa) * T(prm.bz);
-    T pt[6];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) pt[k] = T(p[k]);
-    T s;
-    if constexpr (FIELD) {
-        // parametrised field: Runge-Kutta transport to the barrel's radius or
-        // the disk's z; the covariance is carried by the helix Jacobian in the
-        // path's mean effective axial field
-        const T sth = Tr<T>::sin_(pt[5]);
-        T l;
-        T q[6];
-        int st;
-        if (L.kind != 0) {
-            st = solve_disk_field(pt, T(L.r_or_z), prm, &l, q, evals);
-        } else {
-            T bx, by, bz0;
-            field_at(T(prm.bz), T(prm.field_z0), pt[0], pt[1], pt[2], &bx, &by, &bz0);
-            const T kb0 = T(kKappa) * bz0;
-            st = solve_barrel_field(pt, T(L.r_or_z), prm, kb0, s_init >= T(0) ? s_init / sth : T(-1),
-                                    prm.mlp_max_iter, &l, q, evals, fallbacks);
-        }
-        if (st) return st;
-        field_transport(p, P, q, l, prm, L.kind, T(L.r_or_z), finite);
-        if (material) {
-            if constexpr (MAT)
-                add_material(p, P, L, mat, T(prm.mass));
-            else
-                add_scatter(p, P, L.kind, T(L.x0), T(prm.mass));
-        }
-        if (s_out) *s_out = l * sth;
-        bool fin = true;
-#pragma unroll
-        for (int k = 0; k < 6; ++k) fin &= isfinite(p[k]);
-        return fin ? 0 : KF_ST_NAN;
-    }
-    T st_, ct_;
-    Tr<T>::sincos_(pt[5], &st_, &ct_);
-    if (L.kind == 0) {
-        const T h = -kb * pt[3];
-        T sph, cph;
-        Tr<T>::sincos_(pt[4], &sph, &cph);
-        int st = reach_barrel(pt, h, cph, sph, T(L.r_or_z), prm, s_init, prm.mlp_max_iter, &s, evals,
-                              fallbacks);
-        if (st) return st;
-    } else {
-        if (ct_ == T(0)) return KF_ST_UNREACHABLE;
-        s = (T(L.r_or_z) - pt[2]) * st_ / ct_;
-        *evals += 1;
-        if (s < T(0)) return KF_ST_UNREACHABLE;
-    }
-    transport(p, P, s, kb, L.kind, T(L.r_or_z), st_, ct_, finite);
-    if (material) {
-        if constexpr (MAT)
-            add_material(p, P, L, mat, T(prm.mass));
-        else
-            add_scatter(p, P, L.kind, T(L.x0), T(prm.mass), st_, ct_);
-    }
-    if (s_out) *s_out = s;
-    bool fin = true;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) fin &= isfinite(p[k]);
-    return fin ? 0 : KF_ST_NAN;
-}
 
 // ---------------------------------------------------------------- seed
 template <typename T>
@@ -213,8 +77,6 @@ __global__ __launch_bounds__(256) void propagate_kernel(int64_t n, int64_t ld, T
                                                         MatMap mat, float* __restrict__ path_len,
                                                         int32_t* __restrict__ iters, MlpDev mlp)
 {
-    __shared__ StepLayer<T> sl[kMaxLayers];
-    stage_layers(layers, n_layers, sl);
     const int64_t b0 = (int64_t)blockIdx.x * blockDim.x, i = b0 + threadIdx.x;
     if (!LEARN && i >= n) return;
     const bool inb = i < n;
@@ -233,7 +95,7 @@ __global__ __launch_bounds__(256) void propagate_kernel(int64_t n, int64_t ld, T
     StepLayer<T> L{};
     if (active) {
         load_state(par, cov, ld, b0, threadIdx.x, p, P);
-        L = sl[l];
+        L = step_layer<T>(layers[l]);
     }
     T s_init = T(-1);
     if (LEARN) {
@@ -269,159 +131,6 @@ __global__ __launch_bounds__(256) void propagate_kernel(int64_t n, int64_t ld, T
     status[i] = st;
     if (path_len) path_len[i] = float(s);
     if (iters) iters[i] = ev;
-}
-
-// ---------------------------------------------------------------- fit
-struct FitArgs {
-    int64_t n, ld;
-    void* par;
-    void* cov;
-    void* chi2;
-    int32_t* ndf;
-    uint32_t* status;
-    const float *hx, *hy, *hz, *hsu, *hsv;
-    const int32_t* layer_seq;
-    const int32_t* hit_idx;
-    int64_t n_hits;
-    const kf_layer* layers;
-    int n_layers;
-    kf_params prm;
-    int material;
-    MatMap mat;                  // r-z material map (x0 == nullptr: none)
-    MlpDev mlp;                  // learned guess (KF_INIT_MLP)
-};
-
-// What a step reads besides the state: its layer and hit index, and the hit.
-struct FitIndex {
-    int32_t l, hi;
-};
-struct FitHit {
-    float x, y, z, su, sv;
-};
-
-// Steps [k0, k1) of the fit.  init: start a fresh fit (chi2 = 0, ndf = -5).
-// LEARN: every lane of the wave walks all steps (finished lanes idle), so
-// that the network call at each step is in uniform control flow.
-// The loads run ahead of the arithmetic: while step k is computed, the hit of
-// step k + 1 and the indices of step k + 2 are on their way, so that a step
-// waits for neither of its two dependent loads.
-template <typename T, typename C, typename U, bool LEARN, bool FIELD, bool MAT>
-__global__ __launch_bounds__(256, 2) void fit_kernel(FitArgs a, int k0, int k1, int init)
-{
-    __shared__ StepLayer<T> sl[kMaxLayers];
-    stage_layers(a.layers, a.n_layers, sl);
-    const int64_t b0 = (int64_t)blockIdx.x * blockDim.x;
-    const unsigned i = threadIdx.x;
-    if (!LEARN && b0 + i >= a.n) return;
-    const bool inb = b0 + i < a.n;
-    const int64_t ld = a.ld;
-    T* par = (T*)a.par;
-    T* cov = (T*)a.cov;
-    T* chi2p = (T*)a.chi2 + b0;
-    uint32_t* stp = a.status + b0;
-    int32_t* ndfp = a.ndf + b0;
-    uint32_t st = (init || !inb) ? 0u : stp[i];
-    int32_t ndf = (init || !inb) ? -5 : ndfp[i];
-    U chi2 = (init || !inb) ? U(0) : U(chi2p[i]);
-    bool alive = inb && !(st & kFreezeMask);
-    if (!LEARN && !alive) return;
-    const bool was_alive = alive;
-    auto load_index = [&](int k) {
-        FitIndex x{-1, -1};
-        if (alive && k < k1) {
-            x.l = a.layer_seq ? (a.layer_seq + (k * ld + b0))[i] : k;
-            x.hi = (a.hit_idx + (k * ld + b0))[i];
-        }
-        return x;
-    };
-    auto load_hit = [&](const FitIndex& x) {
-        FitHit h{};
-        if (x.l >= 0 && x.hi >= 0 && x.hi < a.n_hits) {
-            h.x = a.hx[x.hi];
-            h.y = a.hy[x.hi];
-            h.z = a.hz[x.hi];
-            h.su = a.hsu[x.hi];
-            h.sv = a.hsv[x.hi];
-        }
-        return h;
-    };
-    FitIndex now = load_index(k0), next = load_index(k0 + 1);
-    // the state stays in U between steps (rounded to T only when stored)
-    U p[6];
-    C P[21];
-    if (alive) load_state(par, cov, ld, b0, i, p, P);
-    const bool finite = wave_all(!alive || all_finite(P));
-    FitHit hit = load_hit(now);
-    bool touched = false;
-    for (int k = k0; k < k1; ++k) {
-        if (!LEARN && !alive) break;
-        const int32_t l = now.l, hi = now.hi;
-        const FitHit h = hit;
-        now = next;
-        hit = load_hit(next);
-        next = load_index(k + 2);
-        if (alive) {
-            if (l < 0) {
-                alive = false;
-            } else if (l >= a.n_layers) {
-                st |= KF_ST_BADINPUT;
-                alive = false;
-            }
-        }
-        StepLayer<T> L{};
-        if (alive) L = sl[l];
-        T s_init = T(-1);
-        if (LEARN) {
-            float f[kMlpIn] = {0, 0, 0, 0, 0, 0, 0, 0};
-            const bool want = alive && L.kind == 0;
-            if (want) {
-                T pt[6];
-#pragma unroll
-                for (int q = 0; q < 6; ++q) pt[q] = T(p[q]);
-                mlp_features(pt, L, a.prm, f);
-            }
-            const uint64_t wmask = __ballot(want);
-            const float y = wmask ? mlp_wave(a.mlp, f, wmask) : 0.0f;
-            if (want) s_init = T(mlp_guess(f, y));
-        }
-        if (!alive) continue;
-        int ev = 0, fb = 0;
-        int r = propagate_to<T, C, U, FIELD, MAT>(p, P, L, a.prm, a.material != 0, a.mat, finite,
-                                                   s_init, (T*)nullptr, &ev, &fb);
-        touched = true;
-        if (fb) st |= KF_ST_FALLBACK;
-        if (r) {
-            st |= (uint32_t)r;
-            alive = false;
-            continue;
-        }
-        if (hi >= a.n_hits) {
-            st |= KF_ST_BADINPUT;
-            alive = false;
-            continue;
-        }
-        if (hi >= 0) {
-            HitFrame<U> f = hit_frame<U>(h.x, h.y, h.z, h.su, h.sv);
-            U c2 = U(0);
-            r = kf_update<U, C, U>(p, P, f, L.kind, &c2);
-            if (r) {
-                st |= (uint32_t)r;
-                alive = false;
-                continue;
-            }
-            // rounded to storage precision every step, so one launch per step
-            // and one launch for all steps give identical results
-            chi2 = U(T(chi2 + c2));
-            ndf += 2;
-        }
-    }
-    if (!was_alive) return;
-    // on failure the registers hold the last good state (a failed solve or
-    // update leaves them untouched)
-    if (touched) store_state(par, cov, ld, b0, i, p, P);
-    chi2p[i] = T(chi2);
-    ndfp[i] = ndf;
-    stp[i] = st;
 }
 
 // ---------------------------------------------------------------- launchers
@@ -485,17 +194,16 @@ hipError_t launch_propagate(const kf_ctx* ctx, kf_tracks* t, const int32_t* targ
     return hipGetLastError();
 }
 
-template <typename T, typename C, typename U, bool LEARN>
-static void fit_launch(const FitArgs& a, dim3 g, int k0, int k1, int init, bool field, bool map,
-                       hipStream_t s)
+// 64 bits.  At most one workgroup (four waves) a compute unit: one wave a SIMD
+// with all its registers; more tracks: two waves (kf_fit64.hip).  Uniform 1 ..
+// 10 GeV tracks, hits in random order: 60,000 tracks 70 us by one wave and 74 by
+// two, 65,537 110 and 89, 200,000 267 and 254.
+template <bool LEARN>
+static void fit_launch_fp64(const FitArgs& a, dim3 g, int n_cu, int k0, int k1, int init, bool field,
+                            bool map, hipStream_t s)
 {
-    if (field) {
-        if (map) fit_kernel<T, C, U, LEARN, true, true><<<g, 256, 0, s>>>(a, k0, k1, init);
-        else fit_kernel<T, C, U, LEARN, true, false><<<g, 256, 0, s>>>(a, k0, k1, init);
-    } else {
-        if (map) fit_kernel<T, C, U, LEARN, false, true><<<g, 256, 0, s>>>(a, k0, k1, init);
-        else fit_kernel<T, C, U, LEARN, false, false><<<g, 256, 0, s>>>(a, k0, k1, init);
-    }
+    if ((int64_t)g.x <= n_cu) fit_launch<double, double, double, LEARN, 1>(a, g, k0, k1, init, field, map, s);
+    else launch_fit64(a, g, k0, k1, init, LEARN, field, map, s);
 }
 
 hipError_t launch_fit(const kf_ctx* ctx, kf_tracks* t, const kf_hits* h, const int32_t* layer_seq,
@@ -526,7 +234,7 @@ hipError_t launch_fit(const kf_ctx* ctx, kf_tracks* t, const kf_hits* h, const i
     a.mlp = ctx->mlp.dev();
     const bool learn = (flags & KF_INIT_MLP) != 0;
     const int prec = flags & KF_PREC_MASK;
-    dim3 g = grid_for(t->n, 256);
+    dim3 g = grid_for(t->n, kFitThreads);
     const bool per_layer = (flags & KF_PER_LAYER) != 0;
     const bool field = ctx->params.field_z0 > 0.0, map = ctx->mat.x0 != nullptr;
     const int nlaunch = per_layer ? max_steps : 1;
@@ -535,14 +243,14 @@ hipError_t launch_fit(const kf_ctx* ctx, kf_tracks* t, const kf_hits* h, const i
         const int k1 = per_layer ? k + 1 : max_steps;
         const int init = k == 0;
         if (prec == KF_PREC_FP64) {
-            if (learn) fit_launch<double, double, double, true>(a, g, k0, k1, init, field, map, s);
-            else fit_launch<double, double, double, false>(a, g, k0, k1, init, field, map, s);
+            if (learn) fit_launch_fp64<true>(a, g, ctx->n_cu, k0, k1, init, field, map, s);
+            else fit_launch_fp64<false>(a, g, ctx->n_cu, k0, k1, init, field, map, s);
         } else if (prec == KF_PREC_FP32) {
-            if (learn) fit_launch<float, float, float, true>(a, g, k0, k1, init, field, map, s);
-            else fit_launch<float, float, float, false>(a, g, k0, k1, init, field, map, s);
+            if (learn) fit_launch<float, float, float, true, 2>(a, g, k0, k1, init, field, map, s);
+            else fit_launch<float, float, float, false, 2>(a, g, k0, k1, init, field, map, s);
         } else {
-            if (learn) fit_launch<float, double, double, true>(a, g, k0, k1, init, field, map, s);
-            else fit_launch<float, double, double, false>(a, g, k0, k1, init, field, map, s);
+            if (learn) fit_launch<float, double, double, true, 2>(a, g, k0, k1, init, field, map, s);
+            else fit_launch<float, double, double, false, 2>(a, g, k0, k1, init, field, map, s);
         }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
