@@ -202,7 +202,7 @@ template <bool LEARN>
 static void fit_launch_fp64(const FitArgs& a, dim3 g, int n_cu, int k0, int k1, int init, bool field,
                             bool map, hipStream_t s)
 {
-    if ((int64_t)g.x <= n_cu) fit_launch<double, double, double, LEARN, 1>(a, g, k0, k1, init, field, map, s);
+    if ((int64_t)g.x <= n_cu) fit_launch<double, double, double, LEARN, kAnySteps, 1>(a, g, k0, k1, init, field, map, s);
     else launch_fit64(a, g, k0, k1, init, LEARN, field, map, s);
 }
 
@@ -246,11 +246,14 @@ hipError_t launch_fit(const kf_ctx* ctx, kf_tracks* t, const kf_hits* h, const i
             if (learn) fit_launch_fp64<true>(a, g, ctx->n_cu, k0, k1, init, field, map, s);
             else fit_launch_fp64<false>(a, g, ctx->n_cu, k0, k1, init, field, map, s);
         } else if (prec == KF_PREC_FP32) {
-            if (learn) fit_launch<float, float, float, true, 2>(a, g, k0, k1, init, field, map, s);
-            else fit_launch<float, float, float, false, 2>(a, g, k0, k1, init, field, map, s);
+            if (learn) fit_launch<float, float, float, true, kAnySteps, 2>(a, g, k0, k1, init, field, map, s);
+            else fit_launch<float, float, float, false, kAnySteps, 2>(a, g, k0, k1, init, field, map, s);
+        } else if (k1 - k0 == 1) {
+            if (learn) fit_launch<float, double, double, true, kOneStep, 2>(a, g, k0, k1, init, field, map, s);
+            else fit_launch<float, double, double, false, kOneStep, 2>(a, g, k0, k1, init, field, map, s);
         } else {
-            if (learn) fit_launch<float, double, double, true, 2>(a, g, k0, k1, init, field, map, s);
-            else fit_launch<float, double, double, false, 2>(a, g, k0, k1, init, field, map, s);
+            if (learn) fit_launch<float, double, double, true, kManySteps, 2>(a, g, k0, k1, init, field, map, s);
+            else fit_launch<float, double, double, false, kManySteps, 2>(a, g, k0, k1, init, field, map, s);
         }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;

@@ -159,6 +159,7 @@ struct FitArgs {
 };
 
 constexpr int kFitThreads = 256;
+static_assert(kMaxLayers <= kFitThreads, "a workgroup's LDS holds every layer");
 
 // What a step reads besides the state: its layer and hit index, and the hit.
 struct FitIndex {
@@ -168,19 +169,36 @@ struct FitHit {
     float x, y, z, su, sv;
 };
 
+// What the fit kernel is built for: several steps, one (k0), or either.
+enum { kManySteps, kOneStep, kAnySteps };
+
 // Steps [k0, k1) of the fit.  init: start a fresh fit (chi2 = 0, ndf = -5).
 // LEARN: every lane of the wave walks all steps (finished lanes idle), so
 // that the network call at each step is in uniform control flow.
 // The loads run ahead of the arithmetic: while step k is computed, the hit of
 // step k + 1 and the indices of step k + 2 are on their way, so that a step
-// waits for neither of its two dependent loads; the layers wait in LDS.
+// waits for neither of its two dependent loads.  The layers wait in LDS.
+// A launch of one step has nothing to run ahead of, and each lane reads the one
+// layer that it needs: staged behind a barrier before the first load, they were
+// what a small fit by layers waited for.  Loads return in order, so the hit's
+// come last and are waited for at the update.
+// Mixed fits, whose state is rounded between launches anyway, have a kernel for
+// each; the same kernel serves both where one launch and one a layer give the
+// same bits (two copies are fused differently by the compiler).  Fits by
+// layers, staged and now: 2000 tracks in FP32 75 and 71 us, in 64 bits 111 and
+// 88; 200,000 mixed 327 and 315, in 64 bits 547 and 399; 2,000,003 mixed 1404
+// and 1364.
 // WAVES: waves on a SIMD that the registers have to leave room for.
-template <typename T, typename C, typename U, bool LEARN, bool FIELD, bool MAT, int WAVES>
+template <typename T, typename C, typename U, bool LEARN, bool FIELD, bool MAT, int STEPS, int WAVES>
 __global__ __launch_bounds__(kFitThreads, WAVES) void fit_kernel(FitArgs a, int k0, int k1, int init)
 {
-    __shared__ StepLayer<T> sl[kMaxLayers];
-    for (int l = threadIdx.x; l < a.n_layers; l += blockDim.x) sl[l] = step_layer<T>(a.layers[l]);
-    __syncthreads();
+    __shared__ StepLayer<T> sl[STEPS == kOneStep ? 1 : STEPS == kAnySteps ? kFitThreads : kMaxLayers];
+    if constexpr (STEPS == kOneStep) k1 = k0 + 1;
+    const bool one = STEPS == kAnySteps ? k1 - k0 == 1 : STEPS == kOneStep;
+    if (!one) {
+        for (int l = threadIdx.x; l < a.n_layers; l += blockDim.x) sl[l] = step_layer<T>(a.layers[l]);
+        __syncthreads();
+    }
     const int64_t b0 = (int64_t)blockIdx.x * blockDim.x;
     const unsigned i = threadIdx.x;
     if (!LEARN && b0 + i >= a.n) return;
@@ -217,11 +235,16 @@ __global__ __launch_bounds__(kFitThreads, WAVES) void fit_kernel(FitArgs a, int 
         return h;
     };
     FitIndex now = load_index(k0), next = load_index(k0 + 1);
+    StepLayer<T> own{};
+    if (one && now.l >= 0 && now.l < a.n_layers) own = step_layer<T>(a.layers[now.l]);
     // the state stays in U between steps (rounded to T only when stored)
     U p[6];
     C P[21];
     if (alive) load_state(par, cov, ld, b0, i, p, P);
     FitHit hit = load_hit(now);
+    if constexpr (STEPS == kAnySteps) {
+        if (one) sl[i] = own;
+    }
     const bool finite = wave_all(!alive || all_finite(P));
     bool touched = false;
     for (int k = k0; k < k1; ++k) {
@@ -240,7 +263,7 @@ __global__ __launch_bounds__(kFitThreads, WAVES) void fit_kernel(FitArgs a, int 
             }
         }
         StepLayer<T> L{};
-        if (alive) L = sl[l];
+        if (alive) L = STEPS == kOneStep ? own : sl[one ? i : (unsigned)l];
         T s_init = T(-1);
         if (LEARN) {
             float f[kMlpIn] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -272,6 +295,8 @@ __global__ __launch_bounds__(kFitThreads, WAVES) void fit_kernel(FitArgs a, int 
             continue;
         }
         if (hi >= 0) {
+            // (keeps the conversions, and with them the wait, from moving up to the loads)
+            if (STEPS != kManySteps) asm volatile("" : "+v"(h.x), "+v"(h.y), "+v"(h.z), "+v"(h.su), "+v"(h.sv));
             HitFrame<U> f = hit_frame<U>(h.x, h.y, h.z, h.su, h.sv);
             U c2 = U(0);
             r = kf_update<U, C, U>(p, P, f, L.kind, &c2);
@@ -295,16 +320,16 @@ __global__ __launch_bounds__(kFitThreads, WAVES) void fit_kernel(FitArgs a, int 
     stp[i] = st;
 }
 
-template <typename T, typename C, typename U, bool LEARN, int WAVES>
+template <typename T, typename C, typename U, bool LEARN, int STEPS, int WAVES>
 inline void fit_launch(const FitArgs& a, dim3 g, int k0, int k1, int init, bool field, bool map,
                        hipStream_t s)
 {
     if (field) {
-        if (map) fit_kernel<T, C, U, LEARN, true, true, WAVES><<<g, kFitThreads, 0, s>>>(a, k0, k1, init);
-        else fit_kernel<T, C, U, LEARN, true, false, WAVES><<<g, kFitThreads, 0, s>>>(a, k0, k1, init);
+        if (map) fit_kernel<T, C, U, LEARN, true, true, STEPS, WAVES><<<g, kFitThreads, 0, s>>>(a, k0, k1, init);
+        else fit_kernel<T, C, U, LEARN, true, false, STEPS, WAVES><<<g, kFitThreads, 0, s>>>(a, k0, k1, init);
     } else {
-        if (map) fit_kernel<T, C, U, LEARN, false, true, WAVES><<<g, kFitThreads, 0, s>>>(a, k0, k1, init);
-        else fit_kernel<T, C, U, LEARN, false, false, WAVES><<<g, kFitThreads, 0, s>>>(a, k0, k1, init);
+        if (map) fit_kernel<T, C, U, LEARN, false, true, STEPS, WAVES><<<g, kFitThreads, 0, s>>>(a, k0, k1, init);
+        else fit_kernel<T, C, U, LEARN, false, false, STEPS, WAVES><<<g, kFitThreads, 0, s>>>(a, k0, k1, init);
     }
 }
 

@@ -13,8 +13,8 @@ namespace kfmi {
 void launch_fit64(const FitArgs& a, dim3 g, int k0, int k1, int init, bool learn, bool field, bool map,
                   hipStream_t s)
 {
-    if (learn) fit_launch<double, double, double, true, 2>(a, g, k0, k1, init, field, map, s);
-    else fit_launch<double, double, double, false, 2>(a, g, k0, k1, init, field, map, s);
+    if (learn) fit_launch<double, double, double, true, kAnySteps, 2>(a, g, k0, k1, init, field, map, s);
+    else fit_launch<double, double, double, false, kAnySteps, 2>(a, g, k0, k1, init, field, map, s);
 }
 
 }  // namespace kfmi
