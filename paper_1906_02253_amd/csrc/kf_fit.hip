@@ -235,6 +235,7 @@ hipError_t launch_fit(const kf_ctx* ctx, kf_tracks* t, const kf_hits* h, const i
     const bool learn = (flags & KF_INIT_MLP) != 0;
     const int prec = flags & KF_PREC_MASK;
     dim3 g = grid_for(t->n, kFitThreads);
+    a.index_ahead = (int64_t)g.x <= ctx->n_cu || (int64_t)g.x > 3 * (int64_t)ctx->n_cu;
     const bool per_layer = (flags & KF_PER_LAYER) != 0;
     const bool field = ctx->params.field_z0 > 0.0, map = ctx->mat.x0 != nullptr;
     const int nlaunch = per_layer ? max_steps : 1;
