@@ -156,6 +156,7 @@ struct FitArgs {
     int material;
     MatMap mat;                  // r-z material map (x0 == nullptr: none)
     MlpDev mlp;                  // learned guess (KF_INIT_MLP)
+    bool index_ahead;            // FP32: load a step's indices in the step before
 };
 
 constexpr int kFitThreads = 256;
@@ -175,19 +176,28 @@ enum { kManySteps, kOneStep, kAnySteps };
 // Steps [k0, k1) of the fit.  init: start a fresh fit (chi2 = 0, ndf = -5).
 // LEARN: every lane of the wave walks all steps (finished lanes idle), so
 // that the network call at each step is in uniform control flow.
-// The loads run ahead of the arithmetic: while step k is computed, the hit of
-// step k + 1 and the indices of step k + 2 are on their way, so that a step
-// waits for neither of its two dependent loads.  The layers wait in LDS.
-// A launch of one step has nothing to run ahead of, and each lane reads the one
-// layer that it needs: staged behind a barrier before the first load, they were
-// what a small fit by layers waited for.  Loads return in order, so the hit's
-// come last and are waited for at the update.
-// Mixed fits, whose state is rounded between launches anyway, have a kernel for
-// each; the same kernel serves both where one launch and one a layer give the
-// same bits (two copies are fused differently by the compiler).  Fits by
-// layers, staged and now: 2000 tracks in FP32 75 and 71 us, in 64 bits 111 and
-// 88; 200,000 mixed 327 and 315, in 64 bits 547 and 399; 2,000,003 mixed 1404
-// and 1364.
+//
+// Loads: a step's layer and hit indices come in the step before, its hit at its
+// start, to be waited for at the update.  A hit a step earlier still gained
+// nothing where hits come in order (4,000,000 mixed fits 1506 us, now 1485) and
+// cost where they come in any order and the memory is the limit (80,000 mixed
+// fits 98 and 90), except among the Runge-Kutta steps of the field (300,000
+// mixed fits 832 us with it, 870 without).  FP32 fits, with the least
+// arithmetic, do not read the indices ahead either where two or three
+// workgroups share a compute unit and all are resident (with and without, hits
+// in any order: 50,000 tracks 52 us and 55, 80,000 89 and 84, 130,000 128 and
+// 123, 196,608 199 and 198; in order: 100,000 58 and 59, 1,000,000 326 and 336).
+//
+// The layers wait in LDS.  A launch of one step reads the one layer that each
+// lane needs instead: all of them, staged behind a barrier before the first
+// load, were what a small fit by layers waited for.  Loads return in order, so
+// the hit's come last.  Mixed fits, whose state is rounded between launches
+// anyway, have a kernel for one step and one for several; the same kernel serves
+// both where one launch and one a layer give the same bits (two copies are
+// fused differently by the compiler).  Fits by layers with all layers staged and
+// now: 2000 tracks in FP32 72 and 69 us, in 64 bits 110 and 87; 50,000 in 64
+// bits 173 and 113; 200,000 mixed 331 and 322, in 64 bits 540 and 394.
+//
 // WAVES: waves on a SIMD that the registers have to leave room for.
 template <typename T, typename C, typename U, bool LEARN, bool FIELD, bool MAT, int STEPS, int WAVES>
 __global__ __launch_bounds__(kFitThreads, WAVES) void fit_kernel(FitArgs a, int k0, int k1, int init)
@@ -234,26 +244,38 @@ __global__ __launch_bounds__(kFitThreads, WAVES) void fit_kernel(FitArgs a, int 
         }
         return h;
     };
-    FitIndex now = load_index(k0), next = load_index(k0 + 1);
+    constexpr bool kHitAhead = STEPS == kOneStep || (STEPS == kManySteps && FIELD);
+    const bool index_ahead = sizeof(U) == 8 || a.index_ahead;
+    FitIndex now = load_index(k0), next{-1, -1};
+    if (kHitAhead) next = load_index(k0 + 1);
     StepLayer<T> own{};
     if (one && now.l >= 0 && now.l < a.n_layers) own = step_layer<T>(a.layers[now.l]);
     // the state stays in U between steps (rounded to T only when stored)
     U p[6];
     C P[21];
     if (alive) load_state(par, cov, ld, b0, i, p, P);
-    FitHit hit = load_hit(now);
     if constexpr (STEPS == kAnySteps) {
         if (one) sl[i] = own;
     }
+    FitHit hit{};
+    if (kHitAhead) hit = load_hit(now);
     const bool finite = wave_all(!alive || all_finite(P));
     bool touched = false;
     for (int k = k0; k < k1; ++k) {
         if (!LEARN && !alive) break;
+        if (!kHitAhead) {
+            if (!index_ahead && k > k0) now = load_index(k);
+            hit = load_hit(now);
+        }
         const int32_t l = now.l, hi = now.hi;
         FitHit h = hit;
-        now = next;
-        hit = load_hit(next);
-        next = load_index(k + 2);
+        if (kHitAhead) {
+            now = next;
+            hit = load_hit(next);
+            next = load_index(k + 2);
+        } else if (index_ahead) {
+            now = load_index(k + 1);
+        }
         if (alive) {
             if (l < 0) {
                 alive = false;
@@ -296,7 +318,7 @@ __global__ __launch_bounds__(kFitThreads, WAVES) void fit_kernel(FitArgs a, int 
         }
         if (hi >= 0) {
             // (keeps the conversions, and with them the wait, from moving up to the loads)
-            if (STEPS != kManySteps) asm volatile("" : "+v"(h.x), "+v"(h.y), "+v"(h.z), "+v"(h.su), "+v"(h.sv));
+            asm volatile("" : "+v"(h.x), "+v"(h.y), "+v"(h.z), "+v"(h.su), "+v"(h.sv));
             HitFrame<U> f = hit_frame<U>(h.x, h.y, h.z, h.su, h.sv);
             U c2 = U(0);
             r = kf_update<U, C, U>(p, P, f, L.kind, &c2);
