@@ -90,10 +90,15 @@ __device__ inline int block_scan_excl(int v, int* total, int* lds)
 // than seven launches and writing each record twice.  A pass by the one launch
 // and by the two levels: one event of 4200 hits 197 and 220 us, of 56,000 241
 // and 246, of 140,000 327 and 311; four of 56,000 378 and 331; thirty of 6800
-// 312 and 326, ten of 20,400 397 and 404.
-inline bool bin_direct(int64_t n_hits, int n_events)
+// 312 and 326, ten of 20,400 397 and 404.  Only sums are known here, and one
+// event may hold nearly all the hits.  So the one launch also wants an average
+// layer of such an event to fit a workgroup's LDS, with a quarter to spare:
+// beyond it one workgroup works through global memory alone (twelve events on
+// ten layers, 230,000 hits in one of them, 552 us; by the two levels 368).
+inline bool bin_direct(int64_t n_hits, int n_events, int n_layers)
 {
-    return n_hits <= 65536 || (n_hits <= 262144 && n_hits <= (int64_t)n_events * 24576);
+    return n_hits <= 65536 || (n_hits <= 262144 && n_hits <= (int64_t)n_events * 24576 &&
+                               n_hits <= (int64_t)n_layers * 12288);
 }
 constexpr int kDirectShare = 1024;  // hits that a workgroup writes, on average, at least
 constexpr int kDirectSplit = 8;     // workgroups of an (event, layer), at most
@@ -2257,7 +2262,7 @@ hipError_t launch_bin(const FindPlan& pl, const kf_hits* h, const int32_t* event
 {
     hipError_t e;
     const HitView v{h->x, h->y, h->z, h->su, h->sv, h->layer};
-    if (bin_direct(h->n, n_events)) {
+    if (bin_direct(h->n, n_events, n_layers)) {
         int nb_max = 1;
         for (int l = 0; l < n_layers; ++l) {
             const int nb = layers[l].nbin_phi * layers[l].nbin_2;
@@ -2669,7 +2674,7 @@ size_t plan_find(FindPlan* pl, void* base, int64_t n_hits, int n_events, int64_t
     const int64_t nc = (int64_t)n_events * kSeedCells + 1;
     const int64_t ns = n_seeds > 0 ? n_seeds : 1;
     const int64_t nh = n_hits > 0 ? n_hits : 1;
-    const bool direct = bin_direct(n_hits, n_events);
+    const bool direct = bin_direct(n_hits, n_events, n_layers);
     const int64_t nseg = direct ? 0 : (int64_t)n_events * n_layers * bin_split(n_hits, n_events, n_layers) + 1;
     int64_t nsmax = nseg > nc ? nseg : nc;
     if (nh + 1 > nsmax) nsmax = nh + 1;
