@@ -227,21 +227,15 @@ KF_HD inline bool newton_open(T x, T y, T phi, T h, T r_l, T s, int max_it, T to
     return false;
 }
 
-// F P F^T of the transport to a barrel (KIND 0), a disk (KIND 1) or either
-// (KIND -1), the rows of F for x, y, z and phi given (F's other two are unit
-// rows).  A known kind leaves out the products with F's zeros and ones: 158
-// (barrel) and 146 (disk) of the 210 multiplications, in the same order, so
-// the sums are the same for finite P.
-template <int KIND>
+// F P F^T of the transport to a barrel (BARREL) or to any surface, the rows of
+// F for x, y, z and phi given (F's other two are unit rows).  For a barrel the
+// products with F's zeros are left out, which leaves 158 of the 210
+// multiplications, in the same order, so the sums are the same for finite P.
+template <bool BARREL>
 KF_HD constexpr bool transport_nz(int r, int k)
 {
     // row r of F: 0 x, 1 y, 2 z, 3 phi
-    if (KIND == 0) return k == 0 || k == 1 || k == 3 || k == 4 || (r == 2 && (k == 2 || k == 5));
-    if (KIND == 1) {
-        if (r == 2) return k == 2 || k == 5;
-        return k == r || k >= 2;
-    }
-    return true;
+    return !BARREL || k == 0 || k == 1 || k == 3 || k == 4 || (r == 2 && (k == 2 || k == 5));
 }
 
 // Keeps the compiler from interleaving what stands before and after: the rows
@@ -254,7 +248,7 @@ KF_HD inline void sched_fence()
 #endif
 }
 
-template <int KIND, typename T, typename C>
+template <bool BARREL, typename T, typename C>
 KF_HD inline void sandwich(const T F[4][6], C P[21])
 {
     constexpr int gen[4] = {0, 1, 2, 4};       // the general rows of F
@@ -270,7 +264,7 @@ KF_HD inline void sandwich(const T F[4][6], C P[21])
             C acc = C(0);
 #pragma unroll
             for (int k = 0; k < 6; ++k)
-                if (transport_nz<KIND>(r, k)) acc += C(F[r][k]) * P[pk(k, j)];
+                if (transport_nz<BARREL>(r, k)) acc += C(F[r][k]) * P[pk(k, j)];
             A[j] = acc;
         }
 #pragma unroll
@@ -278,7 +272,7 @@ KF_HD inline void sandwich(const T F[4][6], C P[21])
             C acc = C(0);
 #pragma unroll
             for (int k = 0; k < 6; ++k)
-                if (transport_nz<KIND>(q, k)) acc += A[k] * C(F[q][k]);
+                if (transport_nz<BARREL>(q, k)) acc += A[k] * C(F[q][k]);
             Pn[pk(i, gen[q])] = acc;
         }
         if (i < 3) Pn[pk(i, 3)] = A[3];
@@ -289,7 +283,7 @@ KF_HD inline void sandwich(const T F[4][6], C P[21])
         C acc = C(0);
 #pragma unroll
         for (int k = 0; k < 6; ++k)
-            if (transport_nz<KIND>(3, k)) acc += P[pk(3, k)] * C(F[3][k]);
+            if (transport_nz<BARREL>(3, k)) acc += P[pk(3, k)] * C(F[3][k]);
         Pn[pk(3, 4)] = acc;
     }
     Pn[pk(3, 3)] = P[pk(3, 3)];
@@ -369,9 +363,9 @@ KF_HD inline void transport(S p[6], C P[21], T s, T kb, int kind, T zd, T st, T 
     };
     // the sparse product where the whole wave is on barrels
     if (finite && wave_all(kind == 0))
-        sandwich<0>(F, P);
+        sandwich<true>(F, P);
     else
-        sandwich<-1>(F, P);
+        sandwich<false>(F, P);
     p[0] = p[0] + S(s * q.ca * q.sc);
     p[1] = p[1] + S(s * q.sa * q.sc);
     p[2] = p[2] + S(s * cot);
@@ -560,12 +554,12 @@ KF_HD inline U hit_chi2(const T p[6], const C P[21], const HitFrame<U>& f, int k
 // Kalman update with a 2D hit.  Gain K = P H^T S^-1, state x + K r, covariance
 // in Joseph form (I - K H) P (I - K H)^T + K V K^T, evaluated as
 // M = P - K (H P), P+ = M - (M H^T) K^T + K V K^T.  Returns status bits.
-// KIND 0 or 1 (known) or -1 (kind decides): for a barrel the second row of H
+// BARREL (known to be one) or kind decides: for a barrel the second row of H
 // is the unit vector of z, and no products are taken with it.
-template <int KIND, typename T, typename C, typename U>
+template <bool BARREL, typename T, typename C, typename U>
 KF_HD inline int kf_update_kind(T p[6], C P[21], const HitFrame<U>& f, int kind, U* chi2_out)
 {
-    const bool barrel = KIND == 0 || (KIND < 0 && kind == 0);
+    const bool barrel = BARREL || kind == 0;
     const U c = f.c, s = f.s;
     U Pu[21];
 #pragma unroll
@@ -636,8 +630,8 @@ KF_HD inline int kf_update_kind(T p[6], C P[21], const HitFrame<U>& f, int kind,
 template <typename T, typename C, typename U>
 KF_HD inline int kf_update(T p[6], C P[21], const HitFrame<U>& f, int kind, U* chi2_out)
 {
-    if (wave_all(kind == 0)) return kf_update_kind<0, T, C, U>(p, P, f, kind, chi2_out);
-    return kf_update_kind<-1, T, C, U>(p, P, f, kind, chi2_out);
+    if (wave_all(kind == 0)) return kf_update_kind<true, T, C, U>(p, P, f, kind, chi2_out);
+    return kf_update_kind<false, T, C, U>(p, P, f, kind, chi2_out);
 }
 
 // ---------------------------------------------------------------- parametrised field
