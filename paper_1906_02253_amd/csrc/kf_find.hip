@@ -1164,9 +1164,13 @@ constexpr int kAcc = 64 * kScanBatch;
 constexpr int kInsBatch = 4;    // accepted hits an owner loads together
 // Bins from which a window is scanned with its seed's others.  The group scan
 // costs its lists' set-up, and reads the union of windows that may differ; the
-// queue one load per candidate and hit.  64 events of 2100 tracks (128 x 32
-// bins): 2049 us by the queue alone, 1914 from 256 bins on, 1862 from 1024,
-// 1926 from 4096; 16 events with overlapping seeds: 1450, 1232, 1238, 1290.
+// queue one load per candidate and hit.  The line was drawn at 128 x 32 bins a
+// layer: 64 events of 2100 tracks 2049 us by the queue alone, 1914 from 256 bins
+// on, 1862 from 1024, 1926 from 4096; 16 events with overlapping seeds 1450,
+// 1232, 1238, 1290.  It counts bins and not the hits in them; no call became
+// slower for it on other grids (16 events with overlapping seeds by the queue and
+// with it, a grid of 32 x 8, where no window is as long, 1508 and 1283 us; of 512
+// x 32 1518 and 1269).
 constexpr int kLongBins = 1024;
 constexpr int kSelKeys = 64 * (kMaxCands + 1);   // children of a wave's candidates, at most
 
@@ -1706,12 +1710,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
                 // sorted lists over eight lanes each, which a hit enters at once, and
                 // only the hits below a list's last entry do, best first.  A few
                 // low-pT seeds of a large event test 30,000 to 60,000 hits; by the
-                // queue below their hits were loaded once per candidate, 256 at a
-                // time and waited for, and inserted one by one by the owner lane:
-                // 15 to 20 ns a hit, and the longest such seed, 1.2 ms of its own,
-                // ended the pass (16 events with overlapping seeds: 1450 us, now
-                // 1238).  Steered kernels keep to the queue: with the call they
-                // took 661 us for 24 events, without 649.
+                // queue below their hits are loaded once per candidate, 256 at a
+                // time and waited for, and inserted one by one by the owner lane,
+                // and the longest such seed ends the pass (times at kLongBins).
+                // Steered kernels keep to the queue, which their plans' shorter
+                // windows seldom fill: 24 events 661 us with the call, 649 without.
                 uint64_t longs = 0;
                 if constexpr (!STEER) longs = __ballot(pl >= 0 && (int64_t)nrow * (v1 - v0 + 1) >= kLongBins);
                 if (__builtin_expect_with_probability(longs != 0, 0, 0.999))
@@ -1945,10 +1948,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
             // accepted hits, best first, and the child without a hit.  The seed's
             // lanes then take the list's keys in turn, and a key's rank is the
             // number of smaller ones in the list; ranks below max_cands survive.
-            // (One lane merging its seed's sorted lists waited on LDS for every
-            // pick: 2.4 us of a median step's 18; every lane comparing its own
-            // keys with all places of the other lanes' lists took 3.3, most
-            // places being empty.)
+            // (One lane merging its seed's sorted lists waits on LDS for every
+            // pick; every lane comparing its own keys with all places of the other
+            // lanes' lists mostly compares with empty places.)
             const int nk = nacc < MC ? nacc : MC;       // hit children
             wave_fence();                               // the scan's LDS is free
             if (lane_ok) w.sel[s_loc * MC + slot] = ~0ull;
@@ -2103,8 +2105,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KF_FIND_WAV
         // first hit met per layer is kept, then the seed hits where nothing came
         // later.  Each lane loads the entries that its own slot wrote, several
         // steps at once, and the walk follows the chain by shuffles; the layers
-        // already filled are a bit mask.  (One lane chasing the entries and the
-        // filled layers through memory took about 25 us a tile.)
+        // already filled are a bit mask.  (One lane would chase the entries and the
+        // filled layers through memory, a round trip each.)
         {
             int32_t* oh = a.out_hits + (int64_t)sid * nl;
             if (valid)

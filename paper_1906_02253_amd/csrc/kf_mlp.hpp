@@ -43,9 +43,10 @@ __device__ inline uint16_t to_bf16(float f) { return (uint16_t)to_bf16x2(f, f); 
 __device__ inline float from_bf16(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
 // tanh from the exponential: 1 - 2 / (e^{2x} + 1), saturated beyond |x| = 15.
-// The quotient is the correctly rounded one: the division's own refinement of
-// the reciprocal without its scaling, which a denominator of 1 .. 1e13 does
-// not need (2 / d is twice 1 / d to the bit).
+// The quotient is the correctly rounded one, by Markstein's method: the hardware
+// reciprocal refined by fused multiply-adds, then the quotient corrected by its
+// exact remainder.  A denominator of 1 .. 1e13 needs no scaling (2 / d is twice
+// 1 / d to the bit).
 __device__ inline float mlp_tanh(float x)
 {
     x = __builtin_amdgcn_fmed3f(x, -15.0f, 15.0f);
