@@ -81,7 +81,7 @@ KERNEL_SOURCES = ["kf_find.hip", "kf_find.hpp", "kf_math.hpp", "kf_mlp.hpp", "kf
 FIND_KERNEL = "kfmi::find_kernel<float, double, double, false, false, false, false>"
 
 
-FIT_SOURCES = ["kf_fit.hip", "kf_math.hpp", "kf_mlp.hpp", "kf_internal.hpp", "kf_matmap.hpp"]
+FIT_SOURCES = ["kf_fit.hip", "kf_fit.hpp", "kf_math.hpp", "kf_mlp.hpp", "kf_internal.hpp", "kf_matmap.hpp"]
 PER_LAYER_KERNEL = "kfmi::fit_kernel<float, double, double, false, false, false> (per layer)"
 
 
