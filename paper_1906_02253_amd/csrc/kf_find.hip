@@ -91,14 +91,15 @@ __device__ inline int block_scan_excl(int v, int* total, int* lds)
 // and by the two levels: one event of 4200 hits 197 and 220 us, of 56,000 241
 // and 246, of 140,000 327 and 311; four of 56,000 378 and 331; thirty of 6800
 // 312 and 326, ten of 20,400 397 and 404.  Only sums are known here, and one
-// event may hold nearly all the hits.  So the one launch also wants an average
-// layer of such an event to fit a workgroup's LDS, with a quarter to spare:
-// beyond it one workgroup works through global memory alone (twelve events on
-// ten layers, 230,000 hits in one of them, 552 us; by the two levels 368).
+// event may hold nearly all the hits, and layers of more than the LDS holds are
+// left to one workgroup and global memory: so an average layer of such an event
+// may have 16,384 hits, about what the LDS holds.  Ten layers, one event of
+// 155,000 hits among twenty 456 and 367 us, one of 230,000 among twelve 552 and
+// 368; thirty even events of 4200 228 and 246.
 inline bool bin_direct(int64_t n_hits, int n_events, int n_layers)
 {
     return n_hits <= 65536 || (n_hits <= 262144 && n_hits <= (int64_t)n_events * 24576 &&
-                               n_hits <= (int64_t)n_layers * 12288);
+                               n_hits <= (int64_t)n_layers * 16384);
 }
 constexpr int kDirectShare = 1024;  // hits that a workgroup writes, on average, at least
 constexpr int kDirectSplit = 8;     // workgroups of an (event, layer), at most
